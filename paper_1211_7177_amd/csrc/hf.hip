@@ -1,7 +1,8 @@
 // Far field with a truncation order per level (plans built with order <= 0):
 // the S|S, S|R and R|R translations of eqs. 2.20-2.21 by rotation, coaxial
 // shift and rotation back, each target accumulating its own sources in a fixed
-// order.
+// order.  This file builds the tables and runs the orders too large for the
+// matrix-core kernels (rcs_kernel.h) as three launches.
 //
 // A translation by t = (new centre - old centre) of a coefficient vector c
 // (field = sum_nm c_nm F_n^m(x - old centre), F = R or S of eq. 2.16, Y of
@@ -34,7 +35,6 @@
 #include <complex>
 #include <map>
 #include <thread>
-#include <tuple>
 
 #include "plan.h"
 
@@ -45,7 +45,6 @@ namespace {
 using cd = std::complex<double>;
 
 constexpr int HTPB = 256;
-constexpr size_t HF_LDS_MAX = 64 * 1024;
 
 // ------------------------------------------------------------ host functions
 
@@ -244,13 +243,6 @@ void parallel_for(int n, F f) {
 
 // ---------------------------------------------------------------- kernels
 
-struct HfArgs {
-    const void *W;       // rotation table of this translation's polar angle (covers max(ps, pd))
-    const void *ph;      // e^{i m phi}, m = 0.. (covers max(ps, pd))
-    const void *C;       // coaxial block table (pd x ps)
-    int ps, pd;
-};
-
 // decode idx = n^2 + n + m
 __device__ inline void hf_nm(int e, int &n, int &m) {
     n = (int)sqrtf((float)e);
@@ -259,177 +251,10 @@ __device__ inline void hf_nm(int e, int &n, int &m) {
     m = e - n * n - n;
 }
 
-// one translation of CH channel blocks (stride sstr between channels) into acc,
-// with the two scratch vectors b1, b2 (each CH * max(ps, pd)^2)
-template <typename T, int CH>
-__device__ void hf_translate(const cx<T> *__restrict__ src, int64_t sstr, const T *__restrict__ W,
-                             const cx<T> *__restrict__ ph, const cx<T> *__restrict__ C, int ps, int pd, cx<T> *b1,
-                             cx<T> *b2, cx<T> *acc) {
-    const int S2 = ps * ps, D2 = pd * pd;
-    // 1: phases, source order ps
-    for (int t = threadIdx.x; t < CH * S2; t += blockDim.x) {
-        const int c = t / S2, e = t - c * S2;
-        int n, m;
-        hf_nm(e, n, m);
-        const cx<T> f = m >= 0 ? ph[m] : conj(ph[-m]);
-        b1[c * S2 + e] = f * src[c * sstr + e];
-    }
-    __syncthreads();
-    // 2: rotation onto +z, c'_n^m' = sum_m W[n][m][m'] c_n^m
-    for (int t = threadIdx.x; t < CH * S2; t += blockDim.x) {
-        const int c = t / S2, e = t - c * S2;
-        int n, mp;
-        hf_nm(e, n, mp);
-        const T *w = W + (int64_t)n * (2 * n - 1) * (2 * n + 1) / 3 + (mp + n);
-        const cx<T> *x = b1 + c * S2 + n * n;
-        cx<T> s = mk(T(0), T(0));
-        for (int m = 0; m <= 2 * n; ++m) s += w[(int64_t)m * (2 * n + 1)] * x[m];
-        b2[c * S2 + e] = s;
-    }
-    __syncthreads();
-    // 3: coaxial shift, c''_n'^m = sum_n C^|m|_{n'n} c'_n^m, into order pd
-    for (int t = threadIdx.x; t < CH * D2; t += blockDim.x) {
-        const int c = t / D2, e = t - c * D2;
-        int q, m;
-        hf_nm(e, q, m);
-        const int am = m < 0 ? -m : m;
-        cx<T> s = mk(T(0), T(0));
-        if (am < ps) {
-            // block offset sum_{j < am} (pd - j)(ps - j)
-            int64_t off = 0;
-            for (int j = 0; j < am; ++j) off += (int64_t)(pd - j) * (ps - j);
-            const cx<T> *col = C + off + (q - am);
-            const cx<T> *x = b2 + c * S2;
-            for (int n = am; n < ps; ++n) s += col[(int64_t)(n - am) * (pd - am)] * x[n * n + n + m];
-        }
-        b1[c * D2 + e] = s;
-    }
-    __syncthreads();
-    // 4: rotation back, d_n^m' = e^{-i m' phi} sum_m W[n][m'][m] c''_n^m, accumulated;
-    //    W[n][m'][m] = (-1)^(m-m') W[n][m][m'] (Wigner's d^n_{m m'} = (-1)^(m-m') d^n_{m' m}),
-    //    read along m' so that neighbouring threads read neighbouring entries
-    for (int t = threadIdx.x; t < CH * D2; t += blockDim.x) {
-        const int c = t / D2, e = t - c * D2;
-        int n, mp;
-        hf_nm(e, n, mp);
-        const T *w = W + (int64_t)n * (2 * n - 1) * (2 * n + 1) / 3 + (mp + n);
-        const cx<T> *x = b1 + c * D2 + n * n;
-        cx<T> s = mk(T(0), T(0));
-        for (int m = 0; m <= 2 * n; ++m) {
-            const T wm = w[(int64_t)m * (2 * n + 1)];
-            s += (((m + mp + n) & 1) ? -wm : wm) * x[m];
-        }
-        const cx<T> f = mp >= 0 ? conj(ph[mp]) : ph[-mp];
-        acc[c * D2 + e] += f * s;
-    }
-    __syncthreads();
-}
-
-template <typename T, int CH, bool GLB>
-__device__ inline void hf_buffers(cx<T> *smem, cx<T> *gscr, int64_t P2m, int64_t D2, cx<T> *&b1, cx<T> *&b2,
-                                  cx<T> *&acc) {
-    cx<T> *base = smem;
-    if (GLB) base = gscr + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * (2 * CH * P2m + CH * D2);
-    b1 = base;
-    b2 = base + CH * P2m;
-    acc = base + 2 * CH * P2m;
-}
-
-// M2L: target box b of the level sums, in list order, the S|R translations of its
-// far-field sources; writes (overwrites) its local expansion.
-template <typename T, int CH, bool GLB>
-__global__ void __launch_bounds__(HTPB) k_hf_m2l(const int32_t *__restrict__ ff_ofs, const int32_t *__restrict__ ff_src,
-                                                 const int32_t *__restrict__ ff_op, const int32_t *__restrict__ opi,
-                                                 const T *__restrict__ W, int64_t wsz, const cx<T> *__restrict__ ph,
-                                                 const cx<T> *__restrict__ C, int64_t csz, int p, int nrhs_max,
-                                                 const cx<T> *__restrict__ M, cx<T> *__restrict__ Lout, cx<T> *gscr) {
-    extern __shared__ __align__(16) unsigned char hf_smem[];
-    const int b = blockIdx.x;
-    const int col = blockIdx.y * CH;                 // first channel (r * 3 + c) of this block
-    const int r = col / 3, c0 = col % 3;
-    const int64_t P2 = (int64_t)p * p;
-    cx<T> *b1, *b2, *acc;
-    hf_buffers<T, CH, GLB>(reinterpret_cast<cx<T> *>(hf_smem), gscr, P2, P2, b1, b2, acc);
-    for (int t = threadIdx.x; t < CH * P2; t += blockDim.x) acc[t] = mk(T(0), T(0));
-    __syncthreads();
-    const int e0 = ff_ofs[b], e1 = ff_ofs[b + 1];
-    for (int e = e0; e < e1; ++e) {
-        const int s = ff_src[e], o = ff_op[e];
-        const int beta = opi[2 * o], dist = opi[2 * o + 1];
-        hf_translate<T, CH>(M + (((int64_t)s * nrhs_max + r) * 3 + c0) * P2, P2, W + beta * wsz, ph + (int64_t)o * p,
-                            C + dist * csz, p, p, b1, b2, acc);
-    }
-    cx<T> *out = Lout + (((int64_t)b * nrhs_max + r) * 3 + c0) * P2;
-    for (int t = threadIdx.x; t < CH * P2; t += blockDim.x) out[t] = acc[t];
-}
-
-// M2M into parent box b (order pd) from its children (order ps, their own octant
-// directions); writes the parent's multipole.
-template <typename T, int CH, bool GLB>
-__global__ void __launch_bounds__(HTPB) k_hf_m2m(const int32_t *__restrict__ child_start,
-                                                 const int32_t *__restrict__ child_oct, const T *__restrict__ Wo,
-                                                 int64_t wszo, const int32_t *__restrict__ beta_oct,
-                                                 const cx<T> *__restrict__ pho, int pwo, const cx<T> *__restrict__ C,
-                                                 int ps, int pd, int nrhs_max, const cx<T> *__restrict__ Mc,
-                                                 cx<T> *__restrict__ Mp, cx<T> *gscr) {
-    extern __shared__ __align__(16) unsigned char hf_smem[];
-    const int b = blockIdx.x;
-    const int col = blockIdx.y * CH;
-    const int r = col / 3, c0 = col % 3;
-    const int64_t S2 = (int64_t)ps * ps, D2 = (int64_t)pd * pd, P2m = S2 > D2 ? S2 : D2;
-    cx<T> *b1, *b2, *acc;
-    hf_buffers<T, CH, GLB>(reinterpret_cast<cx<T> *>(hf_smem), gscr, P2m, D2, b1, b2, acc);
-    for (int t = threadIdx.x; t < CH * D2; t += blockDim.x) acc[t] = mk(T(0), T(0));
-    __syncthreads();
-    for (int ch = child_start[b]; ch < child_start[b + 1]; ++ch) {
-        const int o = child_oct[ch];
-        hf_translate<T, CH>(Mc + (((int64_t)ch * nrhs_max + r) * 3 + c0) * S2, S2, Wo + beta_oct[o] * wszo,
-                            pho + (int64_t)o * pwo, C, (int)ps, (int)pd, b1, b2, acc);
-    }
-    cx<T> *out = Mp + (((int64_t)b * nrhs_max + r) * 3 + c0) * D2;
-    for (int t = threadIdx.x; t < CH * D2; t += blockDim.x) out[t] = acc[t];
-}
-
-// L2L into child box b (order pd) from its parent (order ps): added to the
-// child's local expansion (which holds its far-field sum).
-template <typename T, int CH, bool GLB>
-__global__ void __launch_bounds__(HTPB) k_hf_l2l(const int32_t *__restrict__ parent, const int32_t *__restrict__ oct,
-                                                 const T *__restrict__ Wo, int64_t wszo,
-                                                 const int32_t *__restrict__ beta_oct, const cx<T> *__restrict__ pho,
-                                                 int pwo, const cx<T> *__restrict__ C, int ps, int pd, int nrhs_max,
-                                                 const cx<T> *__restrict__ Lp, cx<T> *__restrict__ Lc, cx<T> *gscr) {
-    extern __shared__ __align__(16) unsigned char hf_smem[];
-    const int b = blockIdx.x;
-    const int col = blockIdx.y * CH;
-    const int r = col / 3, c0 = col % 3;
-    const int64_t S2 = (int64_t)ps * ps, D2 = (int64_t)pd * pd, P2m = S2 > D2 ? S2 : D2;
-    cx<T> *b1, *b2, *acc;
-    hf_buffers<T, CH, GLB>(reinterpret_cast<cx<T> *>(hf_smem), gscr, P2m, D2, b1, b2, acc);
-    cx<T> *out = Lc + (((int64_t)b * nrhs_max + r) * 3 + c0) * D2;
-    for (int t = threadIdx.x; t < CH * D2; t += blockDim.x) acc[t] = out[t];
-    __syncthreads();
-    const int o = 8 + oct[b];
-    hf_translate<T, CH>(Lp + (((int64_t)parent[b] * nrhs_max + r) * 3 + c0) * S2, S2, Wo + beta_oct[o] * wszo,
-                        pho + (int64_t)o * pwo, C, (int)ps, (int)pd, b1, b2, acc);
-    for (int t = threadIdx.x; t < CH * D2; t += blockDim.x) out[t] = acc[t];
-}
-
 template <typename T>
 __global__ void k_hf_zero(cx<T> *__restrict__ x, int64_t m) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i < m) x[i] = mk(T(0), T(0));
-}
-
-template <typename T>
-size_t hf_lds(int ch, int64_t P2m, int64_t D2) { return (size_t)(2 * ch * P2m + ch * D2) * sizeof(cx<T>); }
-
-// launch mode of a translation stage: 3 channels per block in LDS, 1 in LDS, or
-// 1 with the scratch vectors in global memory (large orders)
-template <typename T>
-int hf_mode(int64_t P2m, int64_t D2) {
-    if (hf_lds<T>(3, P2m, D2) <= HF_LDS_MAX) return 3;
-    if (hf_lds<T>(1, P2m, D2) <= HF_LDS_MAX) return 1;
-    return 0;
 }
 
 // ---------------------------------------------------------------- pipeline
@@ -639,179 +464,6 @@ __global__ void __launch_bounds__(HTPB) k_hf_back(const int32_t *__restrict__ ds
     }
 }
 
-// ------------------------------------------------------- small-order M2L
-// Orders up to 20 (the fine levels, most boxes): one block per (target box,
-// right-hand side), its four wavefronts translating four far-field sources at
-// a time, each in its own LDS buffers.  A lane works on all three channels of
-// a coefficient (one table read serves three).  Each lane keeps J of the
-// target's coefficients in registers (t = lane + 64 j) and adds its
-// wavefront's translations in list order; the four partial sums are added in
-// wavefront order at the end (deterministic).
-constexpr int HFW_WAVES = 4;
-
-template <typename T, int J>
-__global__ void __launch_bounds__(256) k_hf_m2l_w(const int32_t *__restrict__ ff_ofs, const int32_t *__restrict__ ff_src,
-                                                  const int32_t *__restrict__ ff_op, const int32_t *__restrict__ opi,
-                                                  const T *__restrict__ W, int64_t wsz, const cx<T> *__restrict__ ph,
-                                                  const cx<T> *__restrict__ C, int64_t csz, int p, int nrhs_max,
-                                                  const cx<T> *__restrict__ M, cx<T> *__restrict__ Lout) {
-    extern __shared__ __align__(16) unsigned char hf_smem[];
-    const int b = blockIdx.x, r = blockIdx.y;
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int P2 = p * p, N3 = 3 * P2;
-    // per wavefront two vectors of p^2 coefficients x 3 channels, channel-interleaved ([coefficient][3])
-    cx<T> *A = reinterpret_cast<cx<T> *>(hf_smem) + (size_t)wv * 2 * N3;
-    cx<T> *B = A + N3;
-    // tab: (n, m + n) of coefficient t; tab2: (q, m + q) of the t-th coaxial item, ordered (|m|, sign, q)
-    int32_t *tab = reinterpret_cast<int32_t *>(reinterpret_cast<cx<T> *>(hf_smem) + (size_t)HFW_WAVES * 2 * N3);
-    int32_t *tab2 = tab + P2;
-    for (int t = threadIdx.x; t < P2; t += blockDim.x) {
-        int n, m;
-        hf_nm(t, n, m);
-        tab[t] = (n << 10) | (m + n);
-        int am, q;
-        hf_coax_item(t, 0, p, am, m, q);
-        tab2[t] = (q << 10) | (m + q);
-    }
-    cx<T> acc[3 * J];
-#pragma unroll
-    for (int j = 0; j < 3 * J; ++j) acc[j] = mk(T(0), T(0));
-    const int e0 = ff_ofs[b], cnt = ff_ofs[b + 1] - e0;
-    __syncthreads();
-    for (int base = 0; base < cnt; base += HFW_WAVES) {
-        const bool act = base + wv < cnt;
-        int s = 0, o = 0;
-        if (act) {
-            s = ff_src[e0 + base + wv];
-            o = ff_op[e0 + base + wv];
-        }
-        const T *Wb = W + (int64_t)opi[2 * o] * wsz;
-        const cx<T> *Cd = C + (int64_t)opi[2 * o + 1] * csz;
-        const cx<T> *pho = ph + (int64_t)o * p;
-        if (act) {
-            // source coefficients times e^{i m phi}
-            const cx<T> *src = M + ((int64_t)s * nrhs_max + r) * 3 * P2;
-            for (int t = lane; t < P2; t += 64) {
-                const int v = tab[t], n = v >> 10, m = (v & 1023) - n;
-                const cx<T> f = hf_phase(pho, m);
-                A[3 * t] = f * src[t];
-                A[3 * t + 1] = f * src[P2 + t];
-                A[3 * t + 2] = f * src[2 * P2 + t];
-            }
-        }
-        __syncthreads();
-        if (act) {
-            // rotation onto +z: B_n^m' = sum_m W[n][m][m'] A_n^m
-            for (int t = lane; t < P2; t += 64) {
-                const int v = tab[t], n = v >> 10, mpn = v & 1023;
-                const int st = 2 * n + 1;
-                const T *w = Wb + hf_woff(n) + mpn;
-                const cx<T> *x = A + 3 * n * n;
-                cx<T> s0 = mk(T(0), T(0)), s1 = s0, s2 = s0;
-#pragma unroll 4
-                for (int m = 0; m < st; ++m) {
-                    const T wm = w[m * st];
-                    s0 += wm * x[3 * m];
-                    s1 += wm * x[3 * m + 1];
-                    s2 += wm * x[3 * m + 2];
-                }
-                B[3 * t] = s0;
-                B[3 * t + 1] = s1;
-                B[3 * t + 2] = s2;
-            }
-        }
-        __syncthreads();
-        if (act) {
-            // coaxial shift: A_q^m = sum_n C^|m|_{q n} B_n^m
-            for (int t = lane; t < P2; t += 64) {
-                const int v = tab2[t], q = v >> 10, m = (v & 1023) - q;
-                const int am = m < 0 ? -m : m;
-                const int cs = p - am;
-                const cx<T> *col = Cd + hf_coff(am, p, p) + (q - am);
-                const cx<T> *x = B + 3 * (am * am + am + m);
-                cx<T> s0 = mk(T(0), T(0)), s1 = s0, s2 = s0;
-                // input n sits at 3 (n^2 + n + m); successive n are 3 (2n + 2) entries apart
-                int off = 0;
-#pragma unroll 2
-                for (int n = am; n < p; ++n) {
-                    const cx<T> cv = col[(n - am) * cs];
-                    s0 += cv * x[off];
-                    s1 += cv * x[off + 1];
-                    s2 += cv * x[off + 2];
-                    off += 6 * n + 6;
-                }
-                A[3 * (q * q + q + m)] = s0;
-                A[3 * (q * q + q + m) + 1] = s1;
-                A[3 * (q * q + q + m) + 2] = s2;
-            }
-        }
-        __syncthreads();
-        if (act) {
-            // rotation back, d_n^m' = e^{-i m' phi} sum_m W[n][m'][m] c_n^m with W[n][m'][m] =
-            // (-1)^(m-m') W[n][m][m'] read along m': the even-m and odd-m terms are summed apart and
-            // combined with their signs at the end; added to this lane's coefficients
-#pragma unroll
-            for (int j = 0; j < J; ++j) {
-                const int t = lane + 64 * j;
-                if (t < P2) {
-                    const int v = tab[t], n = v >> 10, mpn = v & 1023;
-                    const int st = 2 * n + 1;
-                    const T *w = Wb + hf_woff(n) + mpn;
-                    const cx<T> *x = A + 3 * n * n;
-                    cx<T> e0_ = mk(T(0), T(0)), e1_ = e0_, e2_ = e0_, o0 = e0_, o1 = e0_, o2 = e0_;
-                    int m = 0;
-#pragma unroll 2
-                    for (; m + 1 < st; m += 2) {
-                        const T we = w[m * st], wo = w[(m + 1) * st];
-                        e0_ += we * x[3 * m];
-                        e1_ += we * x[3 * m + 1];
-                        e2_ += we * x[3 * m + 2];
-                        o0 += wo * x[3 * m + 3];
-                        o1 += wo * x[3 * m + 4];
-                        o2 += wo * x[3 * m + 5];
-                    }
-                    {
-                        const T we = w[m * st];           // m = 2n, even
-                        e0_ += we * x[3 * m];
-                        e1_ += we * x[3 * m + 1];
-                        e2_ += we * x[3 * m + 2];
-                    }
-                    // (-1)^(m - m') = (-1)^(m + mpn) for m the index 0..2n
-                    const T sg = (mpn & 1) ? T(-1) : T(1);
-                    const cx<T> f = hf_phase(pho, n - mpn);
-                    const cx<T> fs = sg * f;
-                    acc[3 * j] += fs * (e0_ - o0);
-                    acc[3 * j + 1] += fs * (e1_ - o1);
-                    acc[3 * j + 2] += fs * (e2_ - o2);
-                }
-            }
-        }
-        __syncthreads();
-    }
-    // the four wavefronts' sums, added in wavefront order
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const int t = lane + 64 * j;
-        if (t < P2) {
-            A[3 * t] = acc[3 * j];
-            A[3 * t + 1] = acc[3 * j + 1];
-            A[3 * t + 2] = acc[3 * j + 2];
-        }
-    }
-    __syncthreads();
-    cx<T> *out = Lout + ((int64_t)b * nrhs_max + r) * 3 * P2;
-    const cx<T> *base0 = reinterpret_cast<cx<T> *>(hf_smem);
-    for (int t = threadIdx.x; t < N3; t += blockDim.x) {
-        const int c = t / P2, i = t - c * P2;
-        cx<T> v = base0[3 * i + c];
-        for (int w = 1; w < HFW_WAVES; ++w) v += base0[(size_t)w * 2 * N3 + 3 * i + c];
-        out[t] = v;
-    }
-}
-
-template <typename T>
-size_t hfw_lds(int p) { return (size_t)HFW_WAVES * 2 * 3 * p * p * sizeof(cx<T>) + (size_t)2 * p * p * sizeof(int32_t); }
-
 }  // namespace
 
 // order needed at a level: the low-frequency floor for the tolerance, or the
@@ -827,13 +479,6 @@ int hf_order(double kabs, double side, double tol) {
 
 // per-pair scratch of the pipeline: right-hand sides beyond what fits run in slices
 constexpr size_t HF_PIPE_BYTES = (size_t)2 << 30;
-
-// translation sets whose order exceeds this run as the three-launch pipeline;
-// M2L at orders up to HFW_PMAX runs one source per wavefront
-constexpr int HF_PIPE_P = 20;
-// (its LDS, up to 157 KB per block for FP64 at order 20, fits the CU's 160 KB)
-constexpr int HFW_PMAX = 20;
-constexpr size_t HFW_LDS_MAX = 160 * 1024;
 
 // chunk boundaries of the pipelined launches (one block per pair and chunk): about
 // 256 coefficients per chunk and never more than HF_CHUNK_MAX, which is what the
@@ -884,12 +529,39 @@ static std::vector<int32_t> m_chunks(int pd, int ps, int &maxc) {
     return v;
 }
 
-void build_hf(Plan &P, hipStream_t s) {
+// matrix-core fragments of n rotation / axial tables, converted in parallel and uploaded
+template <typename T, typename F>
+static void upload_frags(DevBuf &d, int n, int64_t size, hipStream_t s, F fill) {
+    std::vector<T> h((size_t)std::max<int64_t>(1, n * size));
+    parallel_for(n, [&](int i) { fill(i, h.data() + (size_t)i * size); });
+    d.alloc(h.size() * sizeof(T));
+    FMB_CHECK_HIP(hipMemcpyAsync(d.p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, s));
+    FMB_CHECK_HIP(hipStreamSynchronize(s));
+}
+
+// rotation tables at the angles beta, axial tables C and phases ph[direction][phs] of a matrix-core set
+template <typename T>
+static void rcs_tables(RcsSet &R, const std::vector<double> &beta, const std::vector<std::vector<cd>> &C,
+                       const std::vector<cd> &ph, int phs, hipStream_t s) {
+    std::vector<cd> f(ph);
+    for (size_t i = 0; i < f.size(); ++i) f[i] *= i % phs ? std::sqrt(0.5) : 0.5;
+    upload_cx<T>(R.ph, f, s);
+    R.phs = phs;
+    const int p = std::max(R.ps, R.pd);
+    upload_frags<T>(R.W, (int)beta.size(), rcs_wsize(R), s, [&](int i, T *out) {
+        std::vector<double> w((size_t)wsize(p));
+        rotation_table(p, beta[i], w.data());
+        rcs_rotation<T>(R, w.data(), out);
+    });
+    upload_frags<T>(R.C, (int)C.size(), rcs_csize(R), s, [&](int i, T *out) { rcs_coaxial<T>(R, C[i].data(), out); });
+}
+
+template <typename T>
+static void build_hf_t(Plan &P, hipStream_t s) {
     const int L = P.depth;
     const int lmin = std::max(2, P.far_lmin);
     const cd k(P.k_re, P.k_im);
     const double kabs = std::abs(k);
-    const bool f64 = P.precision == FMB_FP64;
     std::vector<std::vector<double>> alpha(L + 1);
     for (int l = 0; l <= L; ++l) {
         const double rho = 0.5 * std::sqrt(3.0) * P.ext / (double)(1 << l);
@@ -902,12 +574,16 @@ void build_hf(Plan &P, hipStream_t s) {
         upload_as<double>(P.inv_alpha, ia, s);
     }
     const double c1 = 1.0 / std::sqrt(3.0);
+    std::vector<RcsSet *> sr;
+    constexpr int RCS_PMAX = sizeof(T) == 8 ? RCS_PMAX64 : RCS_PMAX32;
     for (int l = lmin; l <= L; ++l) {
         Level &V = P.lv[l];
         const int p = V.p;
+        const bool mc = p <= RCS_PMAX;            // S|R on the matrix cores, else the three-launch pipeline
         const double side = P.ext / (double)(1 << l);
-        // --- far-field offsets used at this level: polar-angle and distance classes
-        std::vector<int32_t> opi(2 * N_M2L_OPS, 0);
+        // --- far-field offsets used at this level: polar-angle and distance classes; on the matrix cores
+        //     offsets that differ by a reflection in z share a class, which then fixes the distance too
+        std::vector<int32_t> opi(2 * N_M2L_OPS, 0), cls_of(N_M2L_OPS, 0), cdist;
         std::map<std::pair<int, int>, int> bkey, dkey;
         std::vector<double> betas;
         std::vector<double> dists;
@@ -916,124 +592,122 @@ void build_hf(Plan &P, hipStream_t s) {
             if (V.op_start[o + 1] == V.op_start[o]) continue;
             const int dx = o / 49 - 3, dy = (o / 7) % 7 - 3, dz = o % 7 - 3;
             // offset = source - target box coordinates; t = X_t - X_s = -offset * side
-            const double tx = -dx * side, ty = -dy * side, tz = -dz * side;
-            const double T = std::sqrt(tx * tx + ty * ty + tz * tz);
-            const std::pair<int, int> kb{-dz, dx * dx + dy * dy};
-            if (!bkey.count(kb)) {
-                bkey[kb] = (int)betas.size();
-                betas.push_back(std::acos(std::max(-1.0, std::min(1.0, tz / T))));
-            }
+            const double tx = -dx * side, ty = -dy * side, tz = (mc ? std::abs(dz) : -dz) * side;
+            const double T_ = std::sqrt(tx * tx + ty * ty + tz * tz);
             const std::pair<int, int> kd{dx * dx + dy * dy + dz * dz, 0};
             if (!dkey.count(kd)) {
                 dkey[kd] = (int)dists.size();
-                dists.push_back(T);
+                dists.push_back(T_);
+            }
+            const std::pair<int, int> kb{mc ? std::abs(dz) : -dz, dx * dx + dy * dy};
+            if (!bkey.count(kb)) {
+                bkey[kb] = (int)betas.size();
+                betas.push_back(std::acos(std::max(-1.0, std::min(1.0, tz / T_))));
+                cdist.push_back(dkey[kd]);
             }
             opi[2 * o] = bkey[kb];
             opi[2 * o + 1] = dkey[kd];
+            cls_of[o] = bkey[kb] | (dz > 0 ? 1 << 8 : 0);
             const double phi = (dx == 0 && dy == 0) ? 0.0 : std::atan2(ty, tx);
             for (int m = 0; m < p; ++m) ph[(size_t)o * p + m] = std::polar(1.0, m * phi);
         }
-        V.hwsz = wsize(p);
-        V.hcsz = csize(p, p);
-        std::vector<double> Wt((size_t)std::max<size_t>(1, betas.size()) * V.hwsz, 0.0);
-        parallel_for((int)betas.size(), [&](int i) { rotation_table(p, betas[i], Wt.data() + (size_t)i * V.hwsz); });
-        std::vector<cd> Ct((size_t)std::max<size_t>(1, dists.size()) * V.hcsz);
+        std::vector<std::vector<cd>> Ct(dists.size());
         parallel_for((int)dists.size(), [&](int i) {
-            coax_table(CX_SR, k, dists[i], p, p, alpha[l], alpha[l], Ct.data() + (size_t)i * V.hcsz);
+            Ct[i].resize(csize(p, p));
+            coax_table(CX_SR, k, dists[i], p, p, alpha[l], alpha[l], Ct[i].data());
         });
+        if (mc) {
+            if (V.nff > 0) {
+                rcs_shape(V.r_m2l, p, p, V.nbox, sizeof(T) == 8, 16);
+                rcs_tables<T>(V.r_m2l, betas, Ct, ph, p, s);
+                rcs_build(V.r_m2l, V.nff, &V.ff_ofs, &V.ff_src, V.ff_op, 0, cls_of, cdist, s);
+                sr.push_back(&V.r_m2l);
+            }
+        } else {
+            V.hwsz = wsize(p);
+            V.hcsz = csize(p, p);
+            std::vector<double> Wt((size_t)std::max<size_t>(1, betas.size()) * V.hwsz, 0.0);
+            parallel_for((int)betas.size(), [&](int i) { rotation_table(p, betas[i], Wt.data() + (size_t)i * V.hwsz); });
+            std::vector<cd> Call;
+            for (const auto &c : Ct) Call.insert(Call.end(), c.begin(), c.end());
+            upload_cx<T>(V.hph, ph, s);
+            upload_as<T>(V.hW, Wt, s);
+            upload_cx<T>(V.hC, Call, s);
+            upload_as<int32_t>(V.hopi, std::vector<double>(opi.begin(), opi.end()), s);
+        }
         // --- octant directions: 0..7 M2M into this level (t = X_parent - X_child of child octant o),
         //     8..15 L2L into this level (t = X_child - X_parent of own octant o)
         const int pu = l < L ? P.lv[l + 1].p : 0, pdn = l > lmin ? P.lv[l - 1].p : 0;
         V.hpwo = std::max(p, std::max(pu, pdn));
-        V.hwszo = wsize(V.hpwo);
-        std::vector<double> Wo((size_t)2 * V.hwszo);
-        parallel_for(2, [&](int i) { rotation_table(V.hpwo, std::acos(i == 0 ? c1 : -c1), Wo.data() + (size_t)i * V.hwszo); });
         std::vector<cd> pho((size_t)16 * V.hpwo);
-        std::vector<int32_t> boct(16);
+        std::vector<double> oi(32, 0.0);
+        std::vector<int32_t> flips(16);
         for (int q = 0; q < 16; ++q) {
             const int o = q & 7;
             const double sg = q < 8 ? -1.0 : 1.0;
             const double v[3] = {sg * (((o >> 0) & 1) - 0.5), sg * (((o >> 1) & 1) - 0.5), sg * (((o >> 2) & 1) - 0.5)};
-            boct[q] = v[2] > 0 ? 0 : 1;
+            oi[2 * q] = v[2] > 0 ? 0 : 1;
+            flips[q] = v[2] < 0 ? 1 << 8 : 0;
             const double phi = std::atan2(v[1], v[0]);
             for (int m = 0; m < V.hpwo; ++m) pho[(size_t)q * V.hpwo + m] = std::polar(1.0, m * phi);
         }
-        std::vector<cd> Css, Crr;
-        if (l < L) {
-            // S|S from children at level l+1: |t| = sqrt(3)/2 * side_{l+1}
-            Css.resize(csize(p, pu));
-            coax_table(CX_SS, k, 0.5 * std::sqrt(3.0) * side * 0.5, p, pu, alpha[l], alpha[l + 1], Css.data());
+        // S|S from children at level l+1 (|t| = sqrt(3)/2 side_{l+1}), R|R from the parent at level l-1
+        // (|t| = sqrt(3)/2 side_l)
+        const bool up = l < L, down = l > lmin;
+        const bool mcu = std::max(p, pu) <= RCS_PMAX, mcd = std::max(p, pdn) <= RCS_PMAX;
+        std::vector<std::vector<cd>> Css(1), Crr(1);
+        if (up) {
+            Css[0].resize(csize(p, pu));
+            coax_table(CX_SS, k, 0.5 * std::sqrt(3.0) * side * 0.5, p, pu, alpha[l], alpha[l + 1], Css[0].data());
         }
-        if (l > lmin) {
-            // R|R from the parent at level l-1: |t| = sqrt(3)/2 * side_l
-            Crr.resize(csize(p, pdn));
-            coax_table(CX_RR, k, 0.5 * std::sqrt(3.0) * side, p, pdn, alpha[l], alpha[l - 1], Crr.data());
+        if (down) {
+            Crr[0].resize(csize(p, pdn));
+            coax_table(CX_RR, k, 0.5 * std::sqrt(3.0) * side, p, pdn, alpha[l], alpha[l - 1], Crr[0].data());
         }
-        upload_as<int32_t>(V.hopi, std::vector<double>(opi.begin(), opi.end()), s);
-        upload_as<int32_t>(V.hboct, std::vector<double>(boct.begin(), boct.end()), s);
-        {
-            std::vector<double> oi(32, 0.0);
-            for (int q = 0; q < 16; ++q) oi[2 * q] = boct[q];
+        const std::vector<double> b1{std::acos(c1)};
+        if (up && mcu) {
+            Level &C = P.lv[l + 1];
+            rcs_shape(V.r_m2m, pu, p, V.nbox, sizeof(T) == 8, 8);
+            rcs_tables<T>(V.r_m2m, b1, Css, pho, V.hpwo, s);
+            rcs_build(V.r_m2m, C.nbox, &V.child_start, nullptr, C.octant, 0, flips, {0}, s);
+        }
+        if (down && mcd) {
+            rcs_shape(V.r_l2l, pdn, p, V.nbox, sizeof(T) == 8, 8);
+            rcs_tables<T>(V.r_l2l, b1, Crr, pho, V.hpwo, s);
+            rcs_build(V.r_l2l, V.nbox, nullptr, &V.parent, V.octant, 8, flips, {0}, s);
+        }
+        if ((up && !mcu) || (down && !mcd)) {
+            V.hwszo = wsize(V.hpwo);
+            std::vector<double> Wo((size_t)2 * V.hwszo);
+            parallel_for(2, [&](int i) {
+                rotation_table(V.hpwo, std::acos(i == 0 ? c1 : -c1), Wo.data() + (size_t)i * V.hwszo);
+            });
+            upload_cx<T>(V.hpho, pho, s);
+            upload_as<T>(V.hWo, Wo, s);
             upload_as<int32_t>(V.hoinfo, oi, s);
-            const std::vector<int32_t> nc = degree_chunks(p, V.hnck_max), mc = m_chunks(p, p, V.hmck_max),
-                                       mss = m_chunks(p, pu, V.hmck_ss_max), mrr = m_chunks(p, pdn, V.hmck_rr_max);
-            V.hnnck = (int)nc.size() - 1;
-            V.hnmck = (int)mc.size() - 1;
-            V.hnmck_ss = (int)mss.size() - 1;
-            V.hnmck_rr = (int)mrr.size() - 1;
-            upload_as<int32_t>(V.hnck, std::vector<double>(nc.begin(), nc.end()), s);
-            upload_as<int32_t>(V.hmck, std::vector<double>(mc.begin(), mc.end()), s);
-            upload_as<int32_t>(V.hmck_ss, std::vector<double>(mss.begin(), mss.end()), s);
-            upload_as<int32_t>(V.hmck_rr, std::vector<double>(mrr.begin(), mrr.end()), s);
+            if (up && !mcu) upload_cx<T>(V.hCss, Css[0], s);
+            if (down && !mcd) upload_cx<T>(V.hCrr, Crr[0], s);
         }
-        if (f64) {
-            upload_as<double>(V.hW, Wt, s);
-            upload_as<double>(V.hWo, Wo, s);
-            upload_cx<double>(V.hph, ph, s);
-            upload_cx<double>(V.hpho, pho, s);
-            upload_cx<double>(V.hC, Ct, s);
-            upload_cx<double>(V.hCss, Css, s);
-            upload_cx<double>(V.hCrr, Crr, s);
-        } else {
-            upload_as<float>(V.hW, Wt, s);
-            upload_as<float>(V.hWo, Wo, s);
-            upload_cx<float>(V.hph, ph, s);
-            upload_cx<float>(V.hpho, pho, s);
-            upload_cx<float>(V.hC, Ct, s);
-            upload_cx<float>(V.hCss, Css, s);
-            upload_cx<float>(V.hCrr, Crr, s);
-        }
+        const std::vector<int32_t> nc = degree_chunks(p, V.hnck_max), mcs = m_chunks(p, p, V.hmck_max),
+                                   mss = m_chunks(p, pu, V.hmck_ss_max), mrr = m_chunks(p, pdn, V.hmck_rr_max);
+        V.hnnck = (int)nc.size() - 1;
+        V.hnmck = (int)mcs.size() - 1;
+        V.hnmck_ss = (int)mss.size() - 1;
+        V.hnmck_rr = (int)mrr.size() - 1;
+        upload_as<int32_t>(V.hnck, std::vector<double>(nc.begin(), nc.end()), s);
+        upload_as<int32_t>(V.hmck, std::vector<double>(mcs.begin(), mcs.end()), s);
+        upload_as<int32_t>(V.hmck_ss, std::vector<double>(mss.begin(), mss.end()), s);
+        upload_as<int32_t>(V.hmck_rr, std::vector<double>(mrr.begin(), mrr.end()), s);
     }
-    // global scratch for the translation stages whose vectors do not fit in LDS
-    const size_t cs = f64 ? sizeof(cx<double>) : sizeof(cx<float>);
-    size_t need = 0;
-    for (int l = lmin; l <= L; ++l) {
-        const Level &V = P.lv[l];
-        const int64_t P2 = (int64_t)V.p * V.p;
-        const int64_t cols = 3 * (int64_t)P.nrhs_max;
-        auto acc_need = [&](int64_t nb, int64_t P2m, int64_t D2) {
-            const int mode = f64 ? hf_mode<double>(P2m, D2) : hf_mode<float>(P2m, D2);
-            if (mode == 0) need = std::max(need, (size_t)(nb * cols * (2 * P2m + D2)) * cs);
-        };
-        acc_need(V.nbox, P2, P2);
-        if (l < L) {
-            const int64_t S2 = (int64_t)P.lv[l + 1].p * P.lv[l + 1].p;
-            acc_need(V.nbox, std::max(S2, P2), P2);
-        }
-        if (l > lmin) {
-            const int64_t S2 = (int64_t)P.lv[l - 1].p * P.lv[l - 1].p;
-            acc_need(V.nbox, std::max(S2, P2), P2);
-        }
-    }
-    if (need) P.hscratch.alloc(need);
+    rcs_split(sr.data(), (int)sr.size(), sizeof(T) == 8, P.nrhs_max);
     // per-pair vectors of the pipelined translation sets: room for as many right-hand sides as fit
     // HF_PIPE_BYTES (at least one); wider batches run the pipeline over slices of them
     size_t xneed = 0;
     for (int l = lmin; l <= L; ++l) {
         const Level &V = P.lv[l];
         auto use = [&](int64_t npairs, int ps, int pd) {
-            if (std::max(ps, pd) <= HF_PIPE_P) return;
-            const size_t per = (size_t)(npairs * 3 * (int64_t)std::max(ps * ps, pd * pd)) * cs;
+            if (npairs == 0 || std::max(ps, pd) <= RCS_PMAX) return;
+            const size_t per = (size_t)(npairs * 3 * (int64_t)std::max(ps * ps, pd * pd)) * sizeof(cx<T>);
             const int64_t rc = std::max<int64_t>(1, std::min<int64_t>(P.nrhs_max, (int64_t)(HF_PIPE_BYTES / per)));
             xneed = std::max(xneed, per * (size_t)rc);
         };
@@ -1045,6 +719,11 @@ void build_hf(Plan &P, hipStream_t s) {
         P.hX1.alloc(xneed);
         P.hX2.alloc(xneed);
     }
+}
+
+void build_hf(Plan &P, hipStream_t s) {
+    if (P.precision == FMB_FP64) build_hf_t<double>(P, s);
+    else build_hf_t<float>(P, s);
 }
 
 // ------------------------------------------------------------ launches
@@ -1092,107 +771,55 @@ void hf_pipe(Plan &P, int nrhs, hipStream_t s, int64_t npairs, const int32_t *sr
 template <typename T>
 void hf_m2m(Plan &P, int l, int nrhs, hipStream_t s) {
     Level &V = P.lv[l], &Cv = P.lv[l + 1];
-    const int ps = Cv.p, pd = V.p;
-    if (std::max(ps, pd) > HF_PIPE_P) {
-        hf_pipe<T>(P, nrhs, s, Cv.nbox, nullptr, Cv.octant.as<int32_t>(), 0, V.hoinfo.as<int32_t>(), V.hWo.as<T>(),
-                   V.hwszo, V.hpho.as<cx<T>>(), V.hpwo, V.hCss.as<cx<T>>(), 0, Cv, V, V.hmck_ss, V.hnmck_ss,
-                   V.hmck_ss_max, V.nbox, V.child_start.as<int32_t>(), 0, Cv.M.as<cx<T>>(), V.M.as<cx<T>>());
+    if (V.r_m2m.on) {
+        const RcsJob job{&V.r_m2m, Cv.M.p, V.M.p, 0};
+        rcs_run<T>(&job, 1, nrhs, P.nrhs_max, s);
         return;
     }
-    const int64_t S2 = (int64_t)ps * ps, D2 = (int64_t)pd * pd, P2m = std::max(S2, D2);
-    const int mode = hf_mode<T>(P2m, D2);
-    const int ch = mode == 3 ? 3 : 1;
-    const dim3 grid((unsigned)V.nbox, (unsigned)(3 * nrhs / ch));
-    const size_t sh = mode ? hf_lds<T>(ch, P2m, D2) : 0;
-    auto args = std::make_tuple(V.child_start.as<int32_t>(), Cv.octant.as<int32_t>(), V.hWo.as<T>(), V.hwszo,
-                                V.hboct.as<int32_t>(), V.hpho.as<cx<T>>(), V.hpwo, V.hCss.as<cx<T>>(), ps, pd,
-                                P.nrhs_max, Cv.M.as<cx<T>>(), V.M.as<cx<T>>(), P.hscratch.as<cx<T>>());
-    auto go = [&](auto kern) { std::apply([&](auto... a) { kern<<<grid, HTPB, sh, s>>>(a...); }, args); };
-    if (mode == 3) go(k_hf_m2m<T, 3, false>);
-    else if (mode == 1) go(k_hf_m2m<T, 1, false>);
-    else go(k_hf_m2m<T, 1, true>);
-    FMB_LAUNCH_CHECK();
+    hf_pipe<T>(P, nrhs, s, Cv.nbox, nullptr, Cv.octant.as<int32_t>(), 0, V.hoinfo.as<int32_t>(), V.hWo.as<T>(),
+               V.hwszo, V.hpho.as<cx<T>>(), V.hpwo, V.hCss.as<cx<T>>(), 0, Cv, V, V.hmck_ss, V.hnmck_ss,
+               V.hmck_ss_max, V.nbox, V.child_start.as<int32_t>(), 0, Cv.M.as<cx<T>>(), V.M.as<cx<T>>());
 }
 
+// S|R into levels l0 .. l1: the pipelined levels one by one, the others in as few launches as their shapes allow
 template <typename T>
-void hf_m2l(Plan &P, int l, int nrhs, hipStream_t s) {
-    Level &V = P.lv[l];
-    if (V.nff == 0) {
-        // no far-field pairs: the level's local expansions start at zero
-        const int64_t m = V.nbox * P.nrhs_max * 3 * (int64_t)V.p * V.p;
-        k_hf_zero<T><<<(unsigned)((m + HTPB - 1) / HTPB), HTPB, 0, s>>>(V.L.as<cx<T>>(), m);
-        FMB_LAUNCH_CHECK();
-        return;
+void hf_m2l(Plan &P, int l0, int l1, int nrhs, hipStream_t s) {
+    std::vector<RcsJob> jobs;
+    for (int l = l0; l <= l1; ++l) {
+        Level &V = P.lv[l];
+        if (V.nff == 0) {
+            // no far-field pairs: the level's local expansions start at zero
+            const int64_t m = V.nbox * P.nrhs_max * 3 * (int64_t)V.p * V.p;
+            k_hf_zero<T><<<(unsigned)((m + HTPB - 1) / HTPB), HTPB, 0, s>>>(V.L.as<cx<T>>(), m);
+            FMB_LAUNCH_CHECK();
+        } else if (V.r_m2l.on) {
+            jobs.push_back(RcsJob{&V.r_m2l, V.M.p, V.L.p, 0});
+        } else {
+            hf_pipe<T>(P, nrhs, s, V.nff, V.ff_src.as<int32_t>(), V.ff_op.as<int32_t>(), 0, V.hopi.as<int32_t>(),
+                       V.hW.as<T>(), V.hwsz, V.hph.as<cx<T>>(), V.p, V.hC.as<cx<T>>(), V.hcsz, V, V, V.hmck, V.hnmck,
+                       V.hmck_max, V.nbox, V.ff_ofs.as<int32_t>(), 0, V.M.as<cx<T>>(), V.L.as<cx<T>>());
+        }
     }
-    const int p = V.p;
-    if (p > HF_PIPE_P) {
-        hf_pipe<T>(P, nrhs, s, V.nff, V.ff_src.as<int32_t>(), V.ff_op.as<int32_t>(), 0, V.hopi.as<int32_t>(),
-                   V.hW.as<T>(), V.hwsz, V.hph.as<cx<T>>(), p, V.hC.as<cx<T>>(), V.hcsz, V, V, V.hmck, V.hnmck,
-                   V.hmck_max, V.nbox, V.ff_ofs.as<int32_t>(), 0, V.M.as<cx<T>>(), V.L.as<cx<T>>());
-        return;
-    }
-    if (p <= HFW_PMAX && hfw_lds<T>(p) <= HFW_LDS_MAX) {
-        const int J = (p * p + 63) / 64;
-        const size_t sh = hfw_lds<T>(p);
-        auto go = [&](auto kern) {
-            if (sh > 64 * 1024)
-                FMB_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)HFW_LDS_MAX));
-            kern<<<dim3((unsigned)V.nbox, (unsigned)nrhs), 256, sh, s>>>(
-                V.ff_ofs.as<int32_t>(), V.ff_src.as<int32_t>(), V.ff_op.as<int32_t>(), V.hopi.as<int32_t>(), V.hW.as<T>(),
-                V.hwsz, V.hph.as<cx<T>>(), V.hC.as<cx<T>>(), V.hcsz, p, P.nrhs_max, V.M.as<cx<T>>(), V.L.as<cx<T>>());
-        };
-        if (J <= 2) go(k_hf_m2l_w<T, 2>);
-        else if (J <= 3) go(k_hf_m2l_w<T, 3>);
-        else if (J <= 5) go(k_hf_m2l_w<T, 5>);
-        else go(k_hf_m2l_w<T, 7>);
-        FMB_LAUNCH_CHECK();
-        return;
-    }
-    const int64_t P2 = (int64_t)p * p;
-    const int mode = hf_mode<T>(P2, P2);
-    const int ch = mode == 3 ? 3 : 1;
-    const dim3 grid((unsigned)V.nbox, (unsigned)(3 * nrhs / ch));
-    const size_t sh = mode ? hf_lds<T>(ch, P2, P2) : 0;
-    auto args = std::make_tuple(V.ff_ofs.as<int32_t>(), V.ff_src.as<int32_t>(), V.ff_op.as<int32_t>(),
-                                V.hopi.as<int32_t>(), V.hW.as<T>(), V.hwsz, V.hph.as<cx<T>>(), V.hC.as<cx<T>>(),
-                                V.hcsz, p, P.nrhs_max, V.M.as<cx<T>>(), V.L.as<cx<T>>(), P.hscratch.as<cx<T>>());
-    auto go = [&](auto kern) { std::apply([&](auto... a) { kern<<<grid, HTPB, sh, s>>>(a...); }, args); };
-    if (mode == 3) go(k_hf_m2l<T, 3, false>);
-    else if (mode == 1) go(k_hf_m2l<T, 1, false>);
-    else go(k_hf_m2l<T, 1, true>);
-    FMB_LAUNCH_CHECK();
+    rcs_run<T>(jobs.data(), (int)jobs.size(), nrhs, P.nrhs_max, s);
 }
 
 template <typename T>
 void hf_l2l(Plan &P, int l, int nrhs, hipStream_t s) {
     Level &V = P.lv[l], &U = P.lv[l - 1];
-    const int ps = U.p, pd = V.p;
-    if (std::max(ps, pd) > HF_PIPE_P) {
-        hf_pipe<T>(P, nrhs, s, V.nbox, V.parent.as<int32_t>(), V.octant.as<int32_t>(), 8, V.hoinfo.as<int32_t>(),
-                   V.hWo.as<T>(), V.hwszo, V.hpho.as<cx<T>>(), V.hpwo, V.hCrr.as<cx<T>>(), 0, U, V, V.hmck_rr,
-                   V.hnmck_rr, V.hmck_rr_max, V.nbox, nullptr, 1, U.L.as<cx<T>>(), V.L.as<cx<T>>());
+    if (V.r_l2l.on) {
+        const RcsJob job{&V.r_l2l, U.L.p, V.L.p, 1};
+        rcs_run<T>(&job, 1, nrhs, P.nrhs_max, s);
         return;
     }
-    const int64_t S2 = (int64_t)ps * ps, D2 = (int64_t)pd * pd, P2m = std::max(S2, D2);
-    const int mode = hf_mode<T>(P2m, D2);
-    const int ch = mode == 3 ? 3 : 1;
-    const dim3 grid((unsigned)V.nbox, (unsigned)(3 * nrhs / ch));
-    const size_t sh = mode ? hf_lds<T>(ch, P2m, D2) : 0;
-    auto args = std::make_tuple(V.parent.as<int32_t>(), V.octant.as<int32_t>(), V.hWo.as<T>(), V.hwszo,
-                                V.hboct.as<int32_t>(), V.hpho.as<cx<T>>(), V.hpwo, V.hCrr.as<cx<T>>(), ps, pd,
-                                P.nrhs_max, U.L.as<cx<T>>(), V.L.as<cx<T>>(), P.hscratch.as<cx<T>>());
-    auto go = [&](auto kern) { std::apply([&](auto... a) { kern<<<grid, HTPB, sh, s>>>(a...); }, args); };
-    if (mode == 3) go(k_hf_l2l<T, 3, false>);
-    else if (mode == 1) go(k_hf_l2l<T, 1, false>);
-    else go(k_hf_l2l<T, 1, true>);
-    FMB_LAUNCH_CHECK();
+    hf_pipe<T>(P, nrhs, s, V.nbox, V.parent.as<int32_t>(), V.octant.as<int32_t>(), 8, V.hoinfo.as<int32_t>(),
+               V.hWo.as<T>(), V.hwszo, V.hpho.as<cx<T>>(), V.hpwo, V.hCrr.as<cx<T>>(), 0, U, V, V.hmck_rr,
+               V.hnmck_rr, V.hmck_rr_max, V.nbox, nullptr, 1, U.L.as<cx<T>>(), V.L.as<cx<T>>());
 }
 
 template void hf_m2m<float>(Plan &, int, int, hipStream_t);
 template void hf_m2m<double>(Plan &, int, int, hipStream_t);
-template void hf_m2l<float>(Plan &, int, int, hipStream_t);
-template void hf_m2l<double>(Plan &, int, int, hipStream_t);
+template void hf_m2l<float>(Plan &, int, int, int, hipStream_t);
+template void hf_m2l<double>(Plan &, int, int, int, hipStream_t);
 template void hf_l2l<float>(Plan &, int, int, hipStream_t);
 template void hf_l2l<double>(Plan &, int, int, hipStream_t);
 

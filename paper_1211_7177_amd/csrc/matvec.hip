@@ -1468,12 +1468,16 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
         int nk = 0;
         tm.begin(ST_M2L, s, ev);
         if (P.hf) {
-            // each target sums its own far-field translations and writes its local expansion
-            for (int l = lmin; l < L; ++l) hf_m2l<T>(P, l, nrhs, s);
-            hipEvent_t ev2 = nullptr;
-            tm.begin(ST_M2L_FINE, s, ev2);
-            hf_m2l<T>(P, L, nrhs, s);
-            tm.end(ST_M2L_FINE, s, ev2, 1);
+            // each target sums its own far-field translations and writes its local expansion; the finest
+            // level has a launch of its own while its timer is on
+            const bool split = tm.mask >> ST_M2L_FINE & 1u;
+            hf_m2l<T>(P, lmin, split ? L - 1 : L, nrhs, s);
+            if (split) {
+                hipEvent_t ev2 = nullptr;
+                tm.begin(ST_M2L_FINE, s, ev2);
+                hf_m2l<T>(P, L, L, nrhs, s);
+                tm.end(ST_M2L_FINE, s, ev2, 1);
+            }
             tm.end(ST_M2L, s, ev, L - lmin + 1);
             return true;
         }

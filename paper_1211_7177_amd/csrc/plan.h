@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "common.h"
+#include "rcs.h"
 
 namespace fmb {
 
@@ -53,13 +54,13 @@ struct Level {
     DevBuf hph, hpho;           // e^{i m phi}: [343 offsets][p] and [16 octant directions][hpwo]
     DevBuf hC, hCss, hCrr;      // coaxial S|R [distance class][hcsz]; S|S from level+1; R|R from level-1
     DevBuf hopi;                // i32[343][2]: polar-angle class, distance class of each far-field offset
-    DevBuf hboct;               // i32[16]: polar-angle class of each octant direction
     int64_t hwsz = 0, hwszo = 0, hcsz = 0;
     int hpwo = 0;
     DevBuf hoinfo;              // i32[16][2]: polar-angle class (and distance class 0) of each octant direction
     // chunk boundaries of the pipelined launches: degrees n < p, and |m| < p for the
     // coaxial shifts of the S|R set, of the S|S set into this level and of the R|R set into it
     DevBuf hnck, hmck, hmck_ss, hmck_rr;
+    RcsSet r_m2l, r_m2m, r_l2l;   // orders up to RCS_PMAX: S|R, S|S into this level, R|R into this level
     int hnnck = 0, hnmck = 0, hnmck_ss = 0, hnmck_rr = 0;
     int hnck_max = 0, hmck_max = 0, hmck_ss_max = 0, hmck_rr_max = 0;   // largest chunk (coefficients)
 };
@@ -102,7 +103,6 @@ struct Plan {
     // rotation and coaxial shift (order = the leaf level's order)
     bool hf = false;
     double tol = 0.0;
-    DevBuf hscratch;  // vectors of translation stages too large for LDS
     DevBuf hX1, hX2;  // per-pair vectors of the pipelined translations (large orders)
     std::vector<Level> lv;
     // per-node data in Morton order
@@ -145,7 +145,7 @@ void build_basis_tables(Plan &P, hipStream_t s);
 int hf_order(double kabs, double side, double tol);
 void build_hf(Plan &P, hipStream_t s);
 template <typename T> void hf_m2m(Plan &P, int l, int nrhs, hipStream_t s);
-template <typename T> void hf_m2l(Plan &P, int l, int nrhs, hipStream_t s);
+template <typename T> void hf_m2l(Plan &P, int l0, int l1, int nrhs, hipStream_t s);
 template <typename T> void hf_l2l(Plan &P, int l, int nrhs, hipStream_t s);
 void build_corrections(Plan &P, const double *d_pts, const double *d_nrm, const double *d_tri,
                        hipStream_t s);
