@@ -29,6 +29,7 @@ size_t Plan::device_bytes() const {
 void build_tiles(Plan &P, hipStream_t s);
 void split_operators(Plan &P, hipStream_t s);
 void alloc_workspace(Plan &P);
+bool dense_order(int precision, int translate_mode, int p);
 
 // Far-field levels kept for a lossy wavenumber: level l is kept while the
 // damping exp(-Im k h_l) over its box side h_l (the least distance between two
@@ -179,13 +180,17 @@ int fmm_plan(const double *points, const double *normals, const double *weights,
             FMB_REQUIRE(P.order <= 40, "the leaf level needs an order above 40: choose a deeper octree");
             for (int l = 0; l <= P.depth; ++l)
                 FMB_REQUIRE(P.lv[l].p <= 400, "a level needs an order above 400: boxes too large in wavelengths");
-            build_basis_tables(P, s);
-            if (P.far_on()) build_hf(P, s);
         } else {
             for (int l = 0; l <= P.depth; ++l) P.lv[l].p = order;
+            P.dense = dense_order(P.precision, P.translate_mode, order);
+        }
+        build_basis_tables(P, s);
+        if (P.dense) {
             build_operators(P, s);
             build_tiles(P, s);
             split_operators(P, s);
+        } else if (P.far_on()) {
+            build_hf(P, s);
         }
         alloc_workspace(P);
         if (P.corr_mode != FMB_CORR_NONE) {

@@ -1,5 +1,4 @@
-// Far field with a truncation order per level (plans built with order <= 0):
-// the S|S, S|R and R|R translations of eqs. 2.20-2.21 by rotation, coaxial
+// Far field: the S|S, S|R and R|R translations of eqs. 2.20-2.21 by rotation, coaxial
 // shift and rotation back, each target accumulating its own sources in a fixed
 // order.  This file builds the tables and runs the orders too large for the
 // matrix-core kernels (rcs_kernel.h) as three launches.
@@ -87,6 +86,19 @@ std::vector<double> hf_alpha(double x, int p) {
         const double v = x * std::abs(h[n]);
         a[n] = (std::isfinite(v) && v > 1.0) ? 1.0 / v : (std::isfinite(v) ? 1.0 : 1e-300);
         if (a[n] < 1e-300) a[n] = 1e-300;
+    }
+    return a;
+}
+
+// plans of one order: alpha_n = |j_n(i x)| (modified spherical Bessel i_n), which also follows the growth of
+// expansions of moderately lossy k
+std::vector<double> fixed_alpha(double x, int p) {
+    std::vector<cd> j;
+    host_sph_j(cd(0.0, x), p, j);
+    std::vector<double> a(p);
+    for (int n = 0; n < p; ++n) {
+        const double v = std::abs(j[n]);
+        a[n] = v > 1e-300 ? v : 1e-300;
     }
     return a;
 }
@@ -565,7 +577,7 @@ static void build_hf_t(Plan &P, hipStream_t s) {
     std::vector<std::vector<double>> alpha(L + 1);
     for (int l = 0; l <= L; ++l) {
         const double rho = 0.5 * std::sqrt(3.0) * P.ext / (double)(1 << l);
-        alpha[l] = hf_alpha(kabs * rho, std::max(1, P.lv[l].p));
+        alpha[l] = P.hf ? hf_alpha(kabs * rho, std::max(1, P.lv[l].p)) : fixed_alpha(kabs * rho, P.order);
     }
     // 1/alpha at the leaf level for P2M / L2P (row layout [depth+1][order])
     {
@@ -618,7 +630,7 @@ static void build_hf_t(Plan &P, hipStream_t s) {
         });
         if (mc) {
             if (V.nff > 0) {
-                rcs_shape(V.r_m2l, p, p, V.nbox, sizeof(T) == 8, 16);
+                rcs_shape(V.r_m2l, p, p, V.nbox, sizeof(T) == 8, RCS_SR);
                 rcs_tables<T>(V.r_m2l, betas, Ct, ph, p, s);
                 rcs_build(V.r_m2l, V.nff, &V.ff_ofs, &V.ff_src, V.ff_op, 0, cls_of, cdist, s);
                 sr.push_back(&V.r_m2l);
@@ -667,12 +679,12 @@ static void build_hf_t(Plan &P, hipStream_t s) {
         const std::vector<double> b1{std::acos(c1)};
         if (up && mcu) {
             Level &C = P.lv[l + 1];
-            rcs_shape(V.r_m2m, pu, p, V.nbox, sizeof(T) == 8, 8);
+            rcs_shape(V.r_m2m, pu, p, V.nbox, sizeof(T) == 8, RCS_SS);
             rcs_tables<T>(V.r_m2m, b1, Css, pho, V.hpwo, s);
             rcs_build(V.r_m2m, C.nbox, &V.child_start, nullptr, C.octant, 0, flips, {0}, s);
         }
         if (down && mcd) {
-            rcs_shape(V.r_l2l, pdn, p, V.nbox, sizeof(T) == 8, 8);
+            rcs_shape(V.r_l2l, pdn, p, V.nbox, sizeof(T) == 8, RCS_RR);
             rcs_tables<T>(V.r_l2l, b1, Crr, pho, V.hpwo, s);
             rcs_build(V.r_l2l, V.nbox, nullptr, &V.parent, V.octant, 8, flips, {0}, s);
         }

@@ -723,250 +723,20 @@ __global__ void k_zero(cx<T> *__restrict__ x, int64_t m) {
 // with X, Y column blocks of 3*nrhs columns of P2 complex coefficients.  The
 // complex product is done as a real one: a complex column is read as its
 // 2*P2 interleaved (re, im) reals and the operator is stored as the real
-// 2P2 x 2P2 matrix with 2x2 blocks [[re, -im], [im, re]].  Each 64x64 block
-// tile of the real product is computed by four waves of 16x16x4 MFMA
-// instructions with operands staged through LDS.
+// 2P2 x 2P2 matrix with 2x2 blocks [[re, -im], [im, re]].
 struct Tile {
     int32_t op, first, count;
 };
-constexpr int TM = 64, TN = 64, TK = 16;
 constexpr int OS_MAXCOLS = 288;                 // columns per operator-stationary job
 
 
-template <typename T>
-struct Mfma;
-// Operand layout (both types): lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16].
-// Result layout differs: register q of lane l holds D[row][l % 16] with
-//   f64 16x16x4: row = l / 16 + 4 q        f32 16x16x4: row = 4 (l / 16) + q
-// (both checked with an on-device probe).
-template <>
-struct Mfma<double> {
-    typedef double v4 __attribute__((ext_vector_type(4)));
-    __device__ static v4 mma(double a, double b, v4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-    __device__ static int row(int lane, int q) { return (lane >> 4) + 4 * q; }
-};
-template <>
-struct Mfma<float> {
-    typedef float v4 __attribute__((ext_vector_type(4)));
-    __device__ static v4 mma(float a, float b, v4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-    __device__ static int row(int lane, int q) { return 4 * (lane >> 4) + q; }
-};
+typedef float v4f __attribute__((ext_vector_type(4)));
+// FP32 16x16x4: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]; register q of
+// lane l holds D[4 (l / 16) + q][l % 16]
+__device__ inline v4f mma32(float a, float b, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+__device__ inline int mma32_row(int lane, int q) { return 4 * (lane >> 4) + q; }
 
-// Large operators (KR > 128 rows in FP64, > 256 in FP32): block tile of
-// BG_M = 128 rows x big_n<T>() columns (64 in FP64, 128 in FP32), four waves in a
-// 2 x 2 arrangement, each holding 4 x (big_n / 32) MFMA tiles.  K advances BG_K = 16 at a time; the next
-// stage's A and B elements are fetched into registers while the MFMAs run on
-// the current LDS buffer, then stored into the other buffer (one barrier per
-// stage).  A is kept row-major in LDS (pitch BG_K + 1), B k-major (pitch
-// BG_N + 1), so fragment reads and the transposing stores avoid bank conflicts.
-constexpr int BG_M = 128, BG_K = 16;
-// block columns: 64 in FP64 (keeps two waves per SIMD), 128 in FP32
-template <typename T>
-constexpr int big_n() { return sizeof(T) == 8 ? 64 : 128; }
-
-template <typename T, bool ACCUM>
-__global__ void __launch_bounds__(TPB) k_translate_big(const Tile *__restrict__ tiles, int ntiles,
-                                                       const int32_t *__restrict__ ent,
-                                                       const int32_t *__restrict__ src_map,
-                                                       const T *__restrict__ ops, const T *__restrict__ X,
-                                                       T *__restrict__ Y, int KR, int ncol, int64_t blkR) {
-    typedef typename Mfma<T>::v4 v4;
-    constexpr int BG_N = big_n<T>(), NJ = BG_N / 32;          // 16-column MFMA tiles per wave
-    constexpr int AP = BG_K + 1, BP = BG_N + 1;
-    constexpr int LA = BG_M * BG_K / TPB, LB = BG_K * BG_N / TPB;   // elements per thread and stage
-    __shared__ T As[2][BG_M * AP];
-    __shared__ T Bs[2][BG_K * BP];
-    __shared__ int64_t s_in[BG_N], s_out[BG_N];
-    const int tix = xcd_tile(blockIdx.x, ntiles);
-    if (tix >= ntiles) return;
-    const Tile tl = tiles[tix];
-    const int r0 = blockIdx.y * BG_M;
-    const T *Top = ops + (size_t)tl.op * KR * KR;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wr0 = (wave >> 1) * 64, wc0 = (wave & 1) * (BG_N / 2);
-    const int Ctot = tl.count * ncol;
-    const int nk = (KR + BG_K - 1) / BG_K;
-    T pa[LA], pb[LB];
-    for (int c0 = 0; c0 < Ctot; c0 += BG_N) {
-        const int C = min(BG_N, Ctot - c0);
-        __syncthreads();                                  // s_in/s_out and LDS buffers of the previous chunk
-        for (int c = threadIdx.x; c < BG_N; c += blockDim.x) {
-            if (c < C) {
-                const int cg = c0 + c;
-                const int e = cg / ncol, cc = cg % ncol;
-                const int32_t en = ent[tl.first + e];
-                const int32_t sb = src_map ? src_map[en] : en;
-                s_in[c] = (int64_t)sb * blkR + (int64_t)cc * KR;
-                s_out[c] = (int64_t)en * blkR + (int64_t)cc * KR;
-            } else {
-                s_in[c] = -1;
-                s_out[c] = -1;
-            }
-        }
-        __syncthreads();
-        auto fetch = [&](int ks) {
-            const int k0 = ks * BG_K;
-#pragma unroll
-            for (int j = 0; j < LA; ++j) {
-                const int idx = threadIdx.x + j * TPB;
-                const int r = idx / BG_K, kk = idx % BG_K;
-                pa[j] = (r0 + r < KR && k0 + kk < KR) ? Top[(size_t)(r0 + r) * KR + k0 + kk] : T(0);
-            }
-#pragma unroll
-            for (int j = 0; j < LB; ++j) {
-                const int idx = threadIdx.x + j * TPB;
-                const int c = idx / BG_K, kk = idx % BG_K;
-                const int64_t o = s_in[c];
-                pb[j] = (o >= 0 && k0 + kk < KR) ? X[o + k0 + kk] : T(0);
-            }
-        };
-        auto stash = [&](int buf) {
-#pragma unroll
-            for (int j = 0; j < LA; ++j) {
-                const int idx = threadIdx.x + j * TPB;
-                As[buf][(idx / BG_K) * AP + idx % BG_K] = pa[j];
-            }
-#pragma unroll
-            for (int j = 0; j < LB; ++j) {
-                const int idx = threadIdx.x + j * TPB;
-                Bs[buf][(idx % BG_K) * BP + idx / BG_K] = pb[j];
-            }
-        };
-        v4 acc[4][NJ];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) acc[i][j] = v4{0, 0, 0, 0};
-        fetch(0);
-        stash(0);
-        __syncthreads();
-        for (int ks = 0; ks < nk; ++ks) {
-            const int buf = ks & 1;
-            if (ks + 1 < nk) fetch(ks + 1);
-            const T *A = As[buf], *B = Bs[buf];
-#pragma unroll
-            for (int k4 = 0; k4 < BG_K; k4 += 4) {
-                T a[4], b[NJ];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) a[i] = A[(wr0 + 16 * i + (lane & 15)) * AP + k4 + (lane >> 4)];
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) b[j] = B[(k4 + (lane >> 4)) * BP + wc0 + 16 * j + (lane & 15)];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < NJ; ++j) acc[i][j] = Mfma<T>::mma(a[i], b[j], acc[i][j]);
-            }
-            if (ks + 1 < nk) stash(buf ^ 1);
-            __syncthreads();
-        }
-        // ACCUM is a template parameter: the overwrite instance carries no loads of Y
-        if (ACCUM) {
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const int col = wc0 + 16 * j + (lane & 15);
-                if (col >= C) continue;
-                T *yo = Y + s_out[col];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int row = r0 + wr0 + 16 * i + Mfma<T>::row(lane, q);
-                        if (row < KR) yo[row] += acc[i][j][q];
-                    }
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const int col = wc0 + 16 * j + (lane & 15);
-                if (col >= C) continue;
-                T *yo = Y + s_out[col];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int row = r0 + wr0 + 16 * i + Mfma<T>::row(lane, q);
-                        if (row < KR) yo[row] = acc[i][j][q];
-                    }
-            }
-        }
-    }
-}
-
-
-// Variant for small operators (2 p^2 <= 16 RT): every block computes all rows
-// of its 64 columns, so each gathered column is read from memory once.  The
-// four waves split the columns (16 each); every wave holds RT 16x16 tiles.
-template <typename T, int RT>
-__global__ void __launch_bounds__(TPB) k_translate_fm(const Tile *__restrict__ tiles, int ntiles,
-                                                      const int32_t *__restrict__ ent,
-                                                      const int32_t *__restrict__ src_map, const T *__restrict__ ops,
-                                                      const T *__restrict__ X, T *__restrict__ Y, int KR, int ncol,
-                                                      int64_t blkR, int accum) {
-    typedef typename Mfma<T>::v4 v4;
-    __shared__ T As[RT * 16][TK + 1];
-    __shared__ T Bs[TK][TN];
-    __shared__ int32_t s_src[TN], s_dst[TN];
-    const int tix = xcd_tile(blockIdx.x, ntiles);
-    if (tix >= ntiles) return;
-    const Tile tl = tiles[tix];
-    const T *Top = ops + (size_t)tl.op * KR * KR;
-    for (int q = threadIdx.x; q < tl.count && q < TN; q += blockDim.x) {
-        int32_t e = ent[tl.first + q];
-        s_dst[q] = e;
-        s_src[q] = src_map ? src_map[e] : e;
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wc0 = wave * 16;
-    const int Ctot = tl.count * ncol;
-    for (int c0 = 0; c0 < Ctot; c0 += TN) {
-        const int C = min(TN, Ctot - c0);
-        v4 acc[RT];
-#pragma unroll
-        for (int i = 0; i < RT; ++i) acc[i] = v4{0, 0, 0, 0};
-        for (int k0 = 0; k0 < KR; k0 += TK) {
-            __syncthreads();
-            for (int t = threadIdx.x; t < RT * 16 * TK; t += blockDim.x) {
-                const int rr = t / TK, kk = t % TK;
-                As[rr][kk] = (rr < KR && k0 + kk < KR) ? Top[(size_t)rr * KR + k0 + kk] : T(0);
-            }
-            for (int t = threadIdx.x; t < TN * TK; t += blockDim.x) {
-                const int c = t / TK, kk = t % TK;
-                T v = T(0);
-                if (c < C && k0 + kk < KR) {
-                    const int cg = c0 + c;
-                    const int e = cg / ncol, cc = cg % ncol;
-                    v = X[(int64_t)s_src[e] * blkR + (int64_t)cc * KR + k0 + kk];
-                }
-                Bs[kk][c] = v;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int k4 = 0; k4 < TK; k4 += 4) {
-                const T b = Bs[k4 + (lane >> 4)][wc0 + (lane & 15)];
-#pragma unroll
-                for (int i = 0; i < RT; ++i) {
-                    const T a = As[16 * i + (lane & 15)][k4 + (lane >> 4)];
-                    acc[i] = Mfma<T>::mma(a, b, acc[i]);
-                }
-            }
-        }
-        const int col = wc0 + (lane & 15);
-        if (col < C) {
-            const int cg = c0 + col;
-            const int e = cg / ncol, cc = cg % ncol;
-            T *yo = Y + (int64_t)s_dst[e] * blkR + (int64_t)cc * KR;
-#pragma unroll
-            for (int i = 0; i < RT; ++i)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int row = 16 * i + Mfma<T>::row(lane, q);
-                    if (row < KR) yo[row] = accum ? yo[row] + acc[i][q] : acc[i][q];
-                }
-        }
-    }
-}
-
-// Operator-stationary variant for FP32 operators with 2 p^2 <= 164 (p <= 9):
+// Operator-stationary kernel for FP32 operators with 2 p^2 <= 98 (p <= 7):
 // a block owns one operator and a long run of that operator's columns.  Each
 // of its four waves loads the MFMA A-fragments of its RTW row tiles for the
 // whole K extent into registers once (a[i][kk] = T[16 i + l%16][4 kk + l/16]),
@@ -982,7 +752,7 @@ __global__ void __launch_bounds__(TPB) k_translate_os(const Tile *__restrict__ t
                                                       float *__restrict__ Y, int KR, int ncol, int64_t blkR, int accum) {
     constexpr int KP = KS * 4;                     // K padded to whole MFMA k-steps
     constexpr int LD = (KP * OS_COLS + TPB - 1) / TPB;
-    typedef typename Mfma<float>::v4 v4;
+    typedef v4f v4;
     __shared__ float Bs[2][KP][OS_COLS];
     __shared__ int64_t s_in[OS_MAXCOLS], s_out[OS_MAXCOLS];
     const int tix = xcd_tile(blockIdx.x, ntiles);
@@ -1040,7 +810,7 @@ __global__ void __launch_bounds__(TPB) k_translate_os(const Tile *__restrict__ t
         for (int kk = 0; kk < KS; ++kk) {
             const float b = Bs[buf][4 * kk + (lane >> 4)][lane & 15];
 #pragma unroll
-            for (int i = 0; i < RTW; ++i) acc[i] = Mfma<float>::mma(a[i][kk], b, acc[i]);
+            for (int i = 0; i < RTW; ++i) acc[i] = mma32(a[i][kk], b, acc[i]);
         }
         const int cg = t * OS_COLS + (lane & 15);
         if (cg < C) {
@@ -1049,7 +819,7 @@ __global__ void __launch_bounds__(TPB) k_translate_os(const Tile *__restrict__ t
             for (int i = 0; i < RTW; ++i)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int row = (wave * RTW + i) * 16 + Mfma<float>::row(lane, q);
+                    const int row = (wave * RTW + i) * 16 + mma32_row(lane, q);
                     if (row < KR) yo[row] = accum ? yo[row] + acc[i][q] : acc[i][q];
                 }
         }
@@ -1058,31 +828,15 @@ __global__ void __launch_bounds__(TPB) k_translate_os(const Tile *__restrict__ t
     }
 }
 
-// operators with more than 128 (FP64) or 256 (FP32) real rows take k_translate_big
-inline bool use_big(int precision, int KR) {
-    const int rt = (KR + 15) / 16;
-    return !(rt <= 16 && (precision == FMB_FP32 || rt <= 8));
-}
-
 // columns per split-BF16 job (the instantiations in launch_translate)
 inline int bf3_job_cols(int p) { return p <= 5 ? 96 : (p <= 8 ? 64 : 32); }
 
-inline bool use_bf3(const Plan &P) {
-    return P.precision == FMB_FP32 && P.translate_mode == FMB_TRANSLATE_BF16X3 && P.order >= 2 && P.order <= 9;
-}
-
-// the operator-stationary kernel applies to FP32 operators of order 2 <= p <= 9
-inline bool use_os(int precision, int p, int nrhs_max) {
-    (void)nrhs_max;
-    return precision == FMB_FP32 && p >= 2 && p <= 9;
-}
+inline bool use_bf3(const Plan &P) { return P.translate_mode == FMB_TRANSLATE_BF16X3; }
 
 // right-hand sides per translation launch: a job holds whole entries of 3 x (this many)
 // columns, so wider batches run as several launches over slices of the right-hand sides
 inline int translate_rhs_chunk(const Plan &P) {
-    if (use_bf3(P)) return std::min(P.nrhs_max, bf3_job_cols(P.order) / 3);
-    if (use_os(P.precision, P.order, P.nrhs_max)) return std::min(P.nrhs_max, OS_MAXCOLS / 3);
-    return P.nrhs_max;
+    return std::min(P.nrhs_max, (use_bf3(P) ? bf3_job_cols(P.order) : OS_MAXCOLS) / 3);
 }
 
 // Split-BF16 variant of the operator-stationary kernel (FP32 plans, p <= 9).
@@ -1108,7 +862,7 @@ __global__ void __launch_bounds__(TPB) k_translate_bf3(const Tile *__restrict__ 
     constexpr int KP = KS * 32;
     constexpr int CS = KP + 4;                                   // LDS column stride (floats)
     constexpr int LD = (KP * JC + TPB - 1) / TPB;
-    typedef typename Mfma<float>::v4 v4;
+    typedef v4f v4;
     constexpr int RP = 64 * RTW + 1;                             // output tile pitch (rows of 4 waves)
     __shared__ __attribute__((aligned(16))) float Bs[JC][CS];
     __shared__ float Os[16][RP];
@@ -1243,10 +997,9 @@ void launch_bf3(int p, unsigned g, const Tile *tiles, int64_t ntiles, const int3
 
 // role: 0 S|S, 1 S|R, 2 R|R (names the split-BF16 launches in kernel traces);
 // accum: add the products into Y instead of overwriting it
-template <typename T>
-void launch_translate(const Tile *tiles, int64_t ntiles, const int32_t *ent, const int32_t *src_map, const T *ops,
-                      const T *X, T *Y, int KR, int ncol, int64_t blkR, bool os, hipStream_t s, int role, int accum,
-                      const void *fhi = nullptr, const void *flo = nullptr) {
+void launch_translate(const Tile *tiles, int64_t ntiles, const int32_t *ent, const int32_t *src_map, const float *ops,
+                      const float *x, float *y, int KR, int ncol, int64_t blkR, hipStream_t s, int role, int accum,
+                      const void *fhi, const void *flo) {
     if (ntiles <= 0) return;
     if (fhi) {
         // split-BF16 translations (FP32 plans only, checked by use_bf3)
@@ -1258,56 +1011,26 @@ void launch_translate(const Tile *tiles, int64_t ntiles, const int32_t *ent, con
             throw std::runtime_error("split-BF16 translation: unsupported operator size");
         const unsigned g = (unsigned)(((ntiles + 7) / 8) * 8);
         const bf16x8 *h = (const bf16x8 *)fhi, *l = (const bf16x8 *)flo;
-        const float *x = (const float *)X;
-        float *y = (float *)Y;
         switch (role) {
-            case 0: launch_bf3<0>(p, g, tiles, ntiles, ent, src_map, h, l, x, y, KR, RT, ncol, blkR, accum, s); break;
-            case 1: launch_bf3<1>(p, g, tiles, ntiles, ent, src_map, h, l, x, y, KR, RT, ncol, blkR, accum, s); break;
+        case 0: launch_bf3<0>(p, g, tiles, ntiles, ent, src_map, h, l, x, y, KR, RT, ncol, blkR, accum, s); break;
+        case 1: launch_bf3<1>(p, g, tiles, ntiles, ent, src_map, h, l, x, y, KR, RT, ncol, blkR, accum, s); break;
             default: launch_bf3<2>(p, g, tiles, ntiles, ent, src_map, h, l, x, y, KR, RT, ncol, blkR, accum, s); break;
         }
         FMB_LAUNCH_CHECK();
         return;
     }
-    const int rt = (KR + 15) / 16;
     const unsigned g = (unsigned)(((ntiles + 7) / 8) * 8);
-    if (os) {
-        const float *o = (const float *)ops;
-        const float *x = (const float *)X;
-        float *y = (float *)Y;
-        const int p = (int)lround(sqrt(KR / 2.0));
-        switch (p) {
-            case 2: k_translate_os<2, 1><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
-            case 3: k_translate_os<5, 1><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
-            case 4: k_translate_os<8, 1><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
-            case 5: k_translate_os<13, 1><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
-            case 6: k_translate_os<18, 2><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
-            case 7: k_translate_os<25, 2><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
-            case 8: k_translate_os<32, 2><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
-            default: k_translate_os<41, 3><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
-        }
-        FMB_LAUNCH_CHECK();
-        return;
+    const float *o = ops;
+    const int p = (int)lround(sqrt(KR / 2.0));
+    switch (p) {
+        case 2: k_translate_os<2, 1><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
+        case 3: k_translate_os<5, 1><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
+        case 4: k_translate_os<8, 1><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
+        case 5: k_translate_os<13, 1><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
+        case 6: k_translate_os<18, 2><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
+        case 7: k_translate_os<25, 2><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
+        default: throw std::runtime_error("FP32 translation: unsupported operator size");
     }
-#define FMB_FM(R)                                                                                                   \
-    case R:                                                                                                         \
-        k_translate_fm<T, R><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, ops, X, Y, KR, ncol, blkR, accum); \
-        break;
-    if (!use_big(sizeof(T) == 4 ? FMB_FP32 : FMB_FP64, KR)) {
-        switch (rt) {
-            FMB_FM(1) FMB_FM(2) FMB_FM(3) FMB_FM(4) FMB_FM(5) FMB_FM(6) FMB_FM(7) FMB_FM(8)
-            FMB_FM(9) FMB_FM(10) FMB_FM(11) FMB_FM(12) FMB_FM(13) FMB_FM(14) FMB_FM(15) FMB_FM(16)
-            default: break;
-        }
-    } else {
-        const unsigned rowblocks = (unsigned)((KR + BG_M - 1) / BG_M);
-        if (accum)
-            k_translate_big<T, true><<<dim3(g, rowblocks), TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, ops, X, Y, KR,
-                                                                        ncol, blkR);
-        else
-            k_translate_big<T, false><<<dim3(g, rowblocks), TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, ops, X, Y,
-                                                                         KR, ncol, blkR);
-    }
-#undef FMB_FM
     FMB_LAUNCH_CHECK();
 }
 
@@ -1388,7 +1111,6 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
     const int ncol = 3 * nrhs;
     const int KR = 2 * P2;                          // real rows of the embedded operators
     const int64_t blkR = 2 * blk;
-    const bool os = use_os(P.precision, p, P.nrhs_max);
     const bool bf3 = use_bf3(P);
     // translations run over slices of at most cw right-hand sides; roff(r0) is the
     // offset (in reals) of right-hand side r0 inside a box's or slot's block
@@ -1441,7 +1163,7 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
         Level &V = P.lv[l], &C = P.lv[l + 1];
         if (step != k++) continue;
         if (l < lmin) return true;
-        if (P.hf) {
+        if (!P.dense) {
             tm.begin(ST_M2M, s, ev);
             hf_m2m<T>(P, l, nrhs, s);
             tm.end(ST_M2M, s, ev);
@@ -1450,9 +1172,9 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
         if (V.ntiles_m2m == 0) return true;
         tm.begin(ST_M2M, s, ev);
         for (int r0 = 0; r0 < nrhs; r0 += cw)
-            launch_translate<T>(V.tiles_m2m.as<Tile>(), V.ntiles_m2m, C.by_octant.as<int32_t>(), nullptr, V.m2m.as<T>(),
-                                (const T *)C.M.p + roff(r0), (T *)yb + roff(r0), KR, 3 * std::min(cw, nrhs - r0), blkR,
-                                os, s, 0, 0, bf3 ? V.m2m_hi.p : nullptr, V.m2m_lo.p);
+            launch_translate(V.tiles_m2m.as<Tile>(), V.ntiles_m2m, C.by_octant.as<int32_t>(), nullptr, V.m2m.as<float>(),
+                             (const float *)C.M.p + roff(r0), (float *)yb + roff(r0), KR, 3 * std::min(cw, nrhs - r0),
+                             blkR, s, 0, 0, bf3 ? V.m2m_hi.p : nullptr, V.m2m_lo.p);
         tm.end(ST_M2M, s, ev, (nrhs + cw - 1) / cw);
         tm.begin(ST_SUMS, s, ev);
         k_sum_children<T><<<(unsigned)V.nbox, TPB, 0, s>>>(V.child_start.as<int32_t>(), V.nbox, yb, V.M.as<cx<T>>(), blk,
@@ -1467,7 +1189,7 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
         if (!far) return true;
         int nk = 0;
         tm.begin(ST_M2L, s, ev);
-        if (P.hf) {
+        if (!P.dense) {
             // each target sums its own far-field translations and writes its local expansion; the finest
             // level has a launch of its own while its timer is on
             const bool split = tm.mask >> ST_M2L_FINE & 1u;
@@ -1485,10 +1207,10 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
             Level &V = P.lv[l];
             if (V.ntiles_m2l == 0) continue;
             for (int r0 = 0; r0 < nrhs; r0 += cw) {
-                launch_translate<T>(V.tiles_m2l.as<Tile>(), V.ntiles_m2l, V.ff_by_op.as<int32_t>(),
-                                    V.ff_src.as<int32_t>(), V.m2l.as<T>(), (const T *)V.M.p + roff(r0),
-                                    (T *)(yb + V.slot_base * blk) + roff(r0), KR, 3 * std::min(cw, nrhs - r0), blkR,
-                                    os, s, 1, 0, bf3 ? V.m2l_hi.p : nullptr, V.m2l_lo.p);
+                launch_translate(V.tiles_m2l.as<Tile>(), V.ntiles_m2l, V.ff_by_op.as<int32_t>(),
+                                    V.ff_src.as<int32_t>(), V.m2l.as<float>(), (const float *)V.M.p + roff(r0),
+                                 (float *)(yb + V.slot_base * blk) + roff(r0), KR, 3 * std::min(cw, nrhs - r0), blkR,
+                                 s, 1, 0, bf3 ? V.m2l_hi.p : nullptr, V.m2l_lo.p);
                 ++nk;
             }
         }
@@ -1498,7 +1220,7 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
     // Step 3b: the S|R slot sums of every level (one launch, overwriting L),
     // then R|R from the parent added into each level in turn
     if (step == k++) {
-        if (!far || P.hf) return true;
+        if (!far || !P.dense) return true;
         FarSumLevels fs{};
         fs.nlev = L - lmin + 1;
         int64_t tot = 0;
@@ -1521,7 +1243,7 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
         Level &V = P.lv[l];
         if (step != k++) continue;
         if (l <= lmin) return true;
-        if (P.hf) {
+        if (!P.dense) {
             tm.begin(ST_L2L, s, ev);
             hf_l2l<T>(P, l, nrhs, s);
             tm.end(ST_L2L, s, ev);
@@ -1531,9 +1253,9 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
         Level &U = P.lv[l - 1];
         tm.begin(ST_L2L, s, ev);
         for (int r0 = 0; r0 < nrhs; r0 += cw)
-            launch_translate<T>(V.tiles_l2l.as<Tile>(), V.ntiles_l2l, V.by_octant.as<int32_t>(), V.parent.as<int32_t>(),
-                                V.l2l.as<T>(), (const T *)U.L.p + roff(r0), (T *)V.L.p + roff(r0), KR,
-                                3 * std::min(cw, nrhs - r0), blkR, os, s, 2, 1, bf3 ? V.l2l_hi.p : nullptr,
+            launch_translate(V.tiles_l2l.as<Tile>(), V.ntiles_l2l, V.by_octant.as<int32_t>(), V.parent.as<int32_t>(),
+                                V.l2l.as<float>(), (const float *)U.L.p + roff(r0), (float *)V.L.p + roff(r0), KR,
+                             3 * std::min(cw, nrhs - r0), blkR, s, 2, 1, bf3 ? V.l2l_hi.p : nullptr,
                                 V.l2l_lo.p);
         tm.end(ST_L2L, s, ev, (nrhs + cw - 1) / cw);
         return true;
@@ -1614,6 +1336,14 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
 // target job count per launch: about 12 resident blocks on each of the 256 CUs
 constexpr int64_t EP_BLOCKS = 3072;
 
+// Dense operators serve FP32 plans of one order up to 9 with split-BF16 products and up to 7 in FP32: there one small
+// GEMM per offset costs less than walking a class's tiles through LDS.  One product, dense against rotation / shift
+// (ms; torus 60,000 nodes, sphere 3,840): FP32 p = 7 0.60 / 0.57, 0.212 / 0.227; p = 8 0.81 / 0.69, 0.29 / 0.24;
+// split-BF16 p = 9 0.76 / 0.81, 0.235 / 0.263.
+bool dense_order(int precision, int translate_mode, int p) {
+    return precision == FMB_FP32 && p >= 2 && p <= (translate_mode == FMB_TRANSLATE_BF16X3 ? 9 : 7);
+}
+
 void build_tiles(Plan &P, hipStream_t s) {
     const int L = P.depth;
     auto upload = [&](std::vector<Tile> &v, DevBuf &buf, int64_t &cnt) {
@@ -1626,15 +1356,10 @@ void build_tiles(Plan &P, hipStream_t s) {
     // shorter jobs are used until a level spreads over about EP_BLOCKS blocks:
     // a job walks its columns one 16-column chunk after another, so the level's
     // time is set by the longest chain of gathered loads, not by operator traffic.
-    const bool os = use_os(P.precision, P.order, P.nrhs_max);
-    const int cols = use_bf3(P) ? bf3_job_cols(P.order)
-                                : (os ? OS_MAXCOLS
-                                      : (use_big(P.precision, 2 * P.P2)
-                                             ? (P.precision == FMB_FP64 ? big_n<double>() : big_n<float>())
-                                             : TN));
+    const int cols = use_bf3(P) ? bf3_job_cols(P.order) : OS_MAXCOLS;
     const int cw = translate_rhs_chunk(P);
     const int ep_max = std::max(1, cols / (3 * cw));
-    const int ep_min = os ? std::max(1, OS_COLS / (3 * cw)) : ep_max;
+    const int ep_min = std::max(1, OS_COLS / (3 * cw));
     auto ep_for = [&](int64_t total) {
         int64_t e = total / EP_BLOCKS;
         return (int)std::max<int64_t>(ep_min, std::min<int64_t>(ep_max, e));
@@ -1689,8 +1414,8 @@ void split_operators(Plan &P, hipStream_t s) {
 void alloc_workspace(Plan &P) {
     const size_t esz = P.precision == FMB_FP64 ? sizeof(cx<double>) : sizeof(cx<float>);
     const int64_t blk = (int64_t)P.nrhs_max * 3 * P.P2;
-    if (P.hf) {
-        // order per level; the translations need no slot buffer
+    if (!P.dense) {
+        // the translations need no slot buffer
         for (int l = std::max(2, P.far_lmin); l <= P.depth; ++l) {
             Level &V = P.lv[l];
             const int64_t b = (int64_t)P.nrhs_max * 3 * V.p * V.p;

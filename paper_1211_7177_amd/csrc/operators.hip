@@ -1,5 +1,5 @@
-// Translation operators of the upward and downward passes (eqs. 2.20-2.21),
-// built in FP64 on the GPU.
+// Dense translation operators of the upward and downward passes (eqs. 2.20-2.21)
+// for FP32 plans of one small order, built in FP64 on the GPU.
 //
 // Expansions use R_n^m = j_n(k r) Y_n^m and S_n^m = h_n(k r) Y_n^m (eq. 2.16)
 // with Y of eq. 2.15.  From the plane-wave form of the regular solutions,
@@ -300,7 +300,7 @@ void build_operators(Plan &P, hipStream_t s) {
     const int p = P.order, P2 = p * p, L = P.depth;
     const int Lm = 2 * p - 2;
     const int Q = 2 * p + 2;
-    const size_t esz = P.precision == FMB_FP64 ? sizeof(double) : sizeof(float);
+    const size_t esz = sizeof(float);
     DevBuf gx, gw, tab, gaunt;
     gx.alloc(Q * sizeof(double));
     gw.alloc(Q * sizeof(double));
@@ -325,7 +325,6 @@ void build_operators(Plan &P, hipStream_t s) {
         FMB_CHECK_HIP(hipMemcpyAsync(P.inv_alpha.p, hi.data(), hi.size() * sizeof(double), hipMemcpyHostToDevice, s));
         FMB_CHECK_HIP(hipStreamSynchronize(s));
     }
-    build_basis_tables(P, s);
     const size_t shmem = ((size_t)(Lm + 1) * (Lm + 1) + (Lm + 1)) * sizeof(cx<double>);
     auto launch = [&](std::vector<OpDesc> &ds, DevBuf &outbuf, int nslots) {
         outbuf.alloc((size_t)nslots * P2 * P2 * 4 * esz);
@@ -333,14 +332,8 @@ void build_operators(Plan &P, hipStream_t s) {
         DevBuf dd;
         dd.alloc(ds.size() * sizeof(OpDesc));
         FMB_CHECK_HIP(hipMemcpyAsync(dd.p, ds.data(), ds.size() * sizeof(OpDesc), hipMemcpyHostToDevice, s));
-        if (P.precision == FMB_FP64)
-            k_build_op<double><<<(unsigned)ds.size(), TPB, shmem, s>>>(dd.as<OpDesc>(), p, P.k_re, P.k_im,
-                                                                         gaunt.as<double>(), alpha.as<double>(),
-                                                                         outbuf.as<double>());
-        else
-            k_build_op<float><<<(unsigned)ds.size(), TPB, shmem, s>>>(dd.as<OpDesc>(), p, P.k_re, P.k_im,
-                                                                        gaunt.as<double>(), alpha.as<double>(),
-                                                                        outbuf.as<float>());
+        k_build_op<float><<<(unsigned)ds.size(), TPB, shmem, s>>>(dd.as<OpDesc>(), p, P.k_re, P.k_im, gaunt.as<double>(),
+                                                                    alpha.as<double>(), outbuf.as<float>());
         FMB_LAUNCH_CHECK();
         FMB_CHECK_HIP(hipStreamSynchronize(s));
     };

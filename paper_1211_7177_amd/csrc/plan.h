@@ -39,7 +39,7 @@ struct Level {
     // GEMM work tiles (op, first entry, count) for the translations into this level
     DevBuf tiles_m2l, tiles_m2m, tiles_l2l;
     int64_t ntiles_m2l = 0, ntiles_m2m = 0, ntiles_l2l = 0;
-    // operators (precision of the plan), complex [op][P2 (dst)][P2 (src)]
+    // dense plans: operators, complex [op][P2 (dst)][P2 (src)]
     DevBuf m2l;           // [N_M2L_OPS] slots (unused slots left untouched)
     DevBuf m2m;           // [8]: child (level+1) octant -> this level
     DevBuf l2l;           // [8]: parent (level-1) -> child at this level with octant o
@@ -47,7 +47,7 @@ struct Level {
     DevBuf m2l_hi, m2l_lo, m2m_hi, m2m_lo, l2l_hi, l2l_lo;
     // expansions [nbox][nrhs_max][3][P2] complex (P2 = p^2 of this level)
     DevBuf M, L;
-    // plans with an order per level (rotation / coaxial translations, hf.hip)
+    // rotation / coaxial translations (hf.hip)
     int p = 0;                  // truncation order of this level
     DevBuf hW;                  // M2L rotation tables [polar-angle class][hwsz], plan precision
     DevBuf hWo;                 // octant rotation tables [2][hwszo] (cos theta = +-1/sqrt 3)
@@ -99,9 +99,11 @@ struct Plan {
     int far_lmin = 2;
     double rcut2 = 1e300;
     bool far_on() const { return far_lmin <= depth; }
-    // order <= 0 at fmm_plan: an order per level for the tolerance `tol`, translations by
-    // rotation and coaxial shift (order = the leaf level's order)
+    // order <= 0 at fmm_plan: an order per level for the tolerance `tol` (order = the leaf level's order)
     bool hf = false;
+    // FP32 plans of one small order translate by dense operators, one GEMM per offset (matvec.hip); all others by
+    // rotation and coaxial shift (hf.hip)
+    bool dense = false;
     double tol = 0.0;
     DevBuf hX1, hX2;  // per-pair vectors of the pipelined translations (large orders)
     std::vector<Level> lv;
@@ -141,7 +143,7 @@ void gather_nodes(Plan &P, const double *d_pts, const double *d_nrm, const doubl
                   hipStream_t s);
 void build_operators(Plan &P, hipStream_t s);
 void build_basis_tables(Plan &P, hipStream_t s);
-// order per level (hf.hip)
+// rotation / coaxial translations (hf.hip)
 int hf_order(double kabs, double side, double tol);
 void build_hf(Plan &P, hipStream_t s);
 template <typename T> void hf_m2m(Plan &P, int l, int nrhs, hipStream_t s);

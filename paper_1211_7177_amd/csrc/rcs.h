@@ -88,8 +88,9 @@ struct RcsJob {
     int accumulate;
 };
 
-// orders and block shape, before anything else of a set is built; want: destinations per group
-void rcs_shape(RcsSet &R, int ps, int pd, int64_t nbox, bool f64, int want);
+enum RcsKind { RCS_SR, RCS_SS, RCS_RR };
+// orders and block shape, before anything else of a set is built
+void rcs_shape(RcsSet &R, int ps, int pd, int64_t nbox, bool f64, RcsKind kind);
 // fragments of one table in the kernel's layout: W as rotation_table gives it for degrees n < p (p = max(ps, pd)),
 // C as coax_table (pd x ps)
 template <typename T>

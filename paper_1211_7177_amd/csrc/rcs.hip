@@ -10,23 +10,34 @@ namespace fmb {
 
 namespace {
 
-// destinations of sets whose classes were split over zsplit blocks: the partial sums in order
+// destinations of sets whose tiles were split over zsplit blocks: the partial sums in order, all sets of a launch
+struct SumArgs {
+    int nset, nrhs, nrhs_max;
+    int64_t first[RCS_MAXLEV + 1];
+    int zsplit[RCS_MAXLEV], part_rhs[RCS_MAXLEV], blk[RCS_MAXLEV];
+    const void *part[RCS_MAXLEV];
+    void *D[RCS_MAXLEV];
+};
 template <typename T>
-__global__ void k_rcs_sum(const cx<T> *__restrict__ part, int zsplit, int64_t nbox, int nrhs, int part_rhs, int nrhs_max,
-                          int blk, cx<T> *__restrict__ D) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, per = (int64_t)nrhs * blk;
-    if (i >= nbox * per) return;
-    const int64_t box = i / per, e = i - box * per, st = nbox * part_rhs * blk;
-    const cx<T> *p = part + box * part_rhs * blk + e;
+__global__ void k_rcs_sum(SumArgs A) {
+    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= A.first[A.nset]) return;
+    int l = 0;
+    while (A.first[l + 1] <= i) ++l;
+    i -= A.first[l];
+    const int blk = A.blk[l];
+    const int64_t per = (int64_t)A.nrhs * blk, box = i / per, e = i - box * per;
+    const int64_t st = (A.first[l + 1] - A.first[l]) / per * A.part_rhs[l] * blk;
+    const cx<T> *p = (const cx<T> *)A.part[l] + box * A.part_rhs[l] * blk + e;
     cx<T> s = p[0];
-    for (int z = 1; z < zsplit; ++z) s += p[z * st];
-    D[box * nrhs_max * blk + e] = s;
+    for (int z = 1; z < A.zsplit[l]; ++z) s += p[z * st];
+    ((cx<T> *)A.D[l])[box * A.nrhs_max * blk + e] = s;
 }
 
 // Pairs of group g sorted by (class, how many of the destination's pairs of this class came before, destination), one
 // wavefront per group: a tile then meets most destinations once.  Destination b's pairs are ofs[b] .. ofs[b + 1] (b
 // itself without ofs), with sources src[e] (e without src) and directions dir[e] + dir_add.  A pair is packed as
-// destination in group | reflect << 8 | earlier pairs of its tile with its destination << 9 | direction << 12.
+// destination in group | reflect << 8 | earlier pairs of its tile with its destination << 9 | direction << 13.
 constexpr int LIST_TG = 16, LIST_CLS = 40, LIST_OCC = 16;
 
 __global__ void __launch_bounds__(64) k_rcs_lists(const int32_t *__restrict__ ofs, const int32_t *__restrict__ src,
@@ -70,7 +81,7 @@ __global__ void __launch_bounds__(64) k_rcs_lists(const int32_t *__restrict__ of
             __syncthreads();
             if (act && rank == 0) seen[b * LIST_CLS + c] += __popcll(same);
             if (act && rank2 == 0) pos[c * LIST_OCC + occ] += __popcll(eq);
-            if (act && pass) ent[at] = make_int2(src ? src[e] : e, b | (cf >> 8) << 8 | d << 12);
+            if (act && pass) ent[at] = make_int2(src ? src[e] : e, b | (cf >> 8) << 8 | d << 13);
             __syncthreads();
         }
         if (pass == 0) {
@@ -113,15 +124,21 @@ size_t lds_of(const RcsSet &R) {
 
 }  // namespace
 
-void rcs_shape(RcsSet &R, int ps, int pd, int64_t nbox, bool f64, int want) {
+void rcs_shape(RcsSet &R, int ps, int pd, int64_t nbox, bool f64, RcsKind kind) {
     R.ps = ps;
     R.pd = pd;
     R.P = rcs_order(std::max(ps, pd));
     R.nbox = nbox;
     R.nc = f64 ? rcs_nc<double>(R.P) : rcs_nc<float>(R.P);
     R.waves = f64 ? rcs_waves<double>(R.P) : rcs_waves<float>(R.P);
-    // destinations per group: as many as wanted while two blocks (five small ones) share a CU's LDS, at least half
-    // of them; more than that only if one block fills the CU anyway
+    // destinations per group.  S|R: 16, which fill most of a class's tiles; S|S: fewer where a level would
+    // otherwise keep few blocks busy (a group's tiles run one after the other); R|R has one pair for each
+    const int64_t units = nbox * (3 / R.nc);
+    const int want = kind == RCS_SR   ? 16
+                     : kind == RCS_SS ? (int)std::max<int64_t>(1, std::min<int64_t>(8, units / 128))
+                                      : 8;
+    // as many as wanted while two blocks (five small ones) share a CU's LDS, at least half of them; more than that
+    // only if one block fills the CU anyway
     auto lds = [&]() { return f64 ? lds_of<double>(R) : lds_of<float>(R); };
     const size_t budget[3] = {(size_t)31 * 1024, (size_t)79 * 1024, RCS_LDS_MAX};
     R.tg = 0;
@@ -143,27 +160,31 @@ int64_t rcs_csize(const RcsSet &R) { return (int64_t)rcs_map(R.P, R.waves).smax 
 template <typename T>
 static int frag_row(int i) { return sizeof(T) == 8 ? i : i / 4 + 4 * (i % 4); }
 
+// entry (input mi, output mo) of the parity block of degree n; w: that degree's matrix, w[(m + n) st + (m' + n)]
+static double parity_entry(const double *w, int n, int par, int mi, int mo) {
+    const int st = 2 * n + 1;
+    const double a = w[(int64_t)(mi + n) * st + mo + n], c = w[(int64_t)(n - mi) * st + mo + n];
+    if (mi == 0 && mo == 0) return a;
+    if (mi == 0 || mo == 0) return std::sqrt(2.0) * a;
+    return par ? a - c : a + c;
+}
+
 template <typename T>
 void rcs_rotation(const RcsSet &R, const double *W, T *out) {
     const RcsMap M = rcs_map(R.P, R.waves);
     const int p = std::max(R.ps, R.pd);
-    const double q2 = std::sqrt(2.0);
     std::fill(out, out + rcs_wsize(R), T(0));
     for (int n = 0; n < p; ++n)
         for (int par = 0; par < 2; ++par) {
             if (M.rw[2 * n + par] < 0) continue;
-            const int b = n + 1 - par, ks = (b + 3) / 4, rt = (b + 15) / 16, st = 2 * n + 1;
-            const double *w = W + (int64_t)n * (2 * n - 1) * (2 * n + 1) / 3;      // w[(m + n) st + (m' + n)]
+            const int b = n + 1 - par, ks = (b + 3) / 4, rt = (b + 15) / 16;
+            const double *w = W + (int64_t)n * (2 * n - 1) * (2 * n + 1) / 3;
             T *o = out + ((int64_t)M.rw[2 * n + par] * M.rmax + M.ro[2 * n + par]) * 64;
             for (int i = 0; i < rt; ++i)
                 for (int k = 0; k < ks; ++k)
                     for (int l = 0; l < 64; ++l, ++o) {
                         const int mo = 16 * i + frag_row<T>(l & 15) + par, mi = 4 * k + (l >> 4) + par;
-                        if (mo > n || mi > n) continue;
-                        const double a = w[(int64_t)(mi + n) * st + mo + n], c = w[(int64_t)(n - mi) * st + mo + n];
-                        if (mi == 0 && mo == 0) *o = (T)a;
-                        else if (mi == 0 || mo == 0) *o = (T)(q2 * a);
-                        else *o = (T)(par ? a - c : a + c);
+                        if (mo <= n && mi <= n) *o = (T)parity_entry(w, n, par, mi, mo);
                     }
         }
 }
@@ -215,14 +236,22 @@ void rcs_build(RcsSet &R, int64_t npairs, const DevBuf *ofs, const DevBuf *src, 
     FMB_CHECK_HIP(hipStreamSynchronize(s));
 }
 
-// Sets of few blocks split each group's tiles over zsplit of them, so that a launch over all levels fills the chip
-// a few times over; the partial sums stay under 256 MB.
+// Sets of few blocks split each group's tiles over zsplit of them, so that a launch over all levels holds at least
+// twice what the CUs take at once (by LDS, eight blocks at most); the partial sums stay under 256 MB.  S|R of all
+// levels, unsplit -> split: ring 148k FP64 p = 16 1.82 -> 1.34 ms, 26k ellipsoid FP32 p = 12 1.0 -> 0.48 ms, sphere
+// 3,840 nodes FP64 p = 16 (123 blocks) 0.30 ms at 6 ways, 0.28 at 8 to 16, 0.30 at 25.
 void rcs_split(RcsSet **sets, int nsets, bool f64, int nrhs_max) {
     int64_t blocks = 0;
-    for (int i = 0; i < nsets; ++i) blocks += (int64_t)sets[i]->ngroups * (3 / sets[i]->nc);
-    int want = 768, zmax = 8;
-    if (blocks == 0 || blocks >= want) return;
-    const int z = (int)std::min<int64_t>(zmax, (want + blocks - 1) / blocks);
+    size_t lds = 1;
+    for (int i = 0; i < nsets; ++i) {
+        blocks += (int64_t)sets[i]->ngroups * (3 / sets[i]->nc);
+        lds = std::max(lds, sets[i]->lds);
+    }
+    blocks *= nrhs_max;              // a plan for batches is split for batches
+    if (blocks == 0) return;
+    const int64_t want = 512 * (int64_t)std::min<size_t>(8, RCS_LDS_MAX / lds);
+    const int z = (int)std::min<int64_t>(32, (want + blocks - 1) / blocks);
+    if (z <= 1) return;
     for (int i = 0; i < nsets; ++i) {
         RcsSet &R = *sets[i];
         const size_t per = (size_t)z * R.nbox * 3 * R.pd * R.pd * (f64 ? 16 : 8);
@@ -298,14 +327,22 @@ void rcs_run(const RcsJob *jobs, int njobs, int nrhs, int nrhs_max, hipStream_t 
             if (blocks == 0) continue;
             FMB_REQUIRE(blocks < ((int64_t)1 << 31), "too many translation blocks");
             launch(T(0), F.P, A, (unsigned)blocks, lds, s);
+            SumArgs Z{};
+            Z.nrhs = nr;
+            Z.nrhs_max = nrhs_max;
             for (int i = a; i < b; ++i) {
                 const RcsSet &R = *jobs[i].set;
                 if (R.zsplit == 1) continue;
-                const int blk = 3 * R.pd * R.pd;
-                const int64_t m = R.nbox * nr * blk;
-                k_rcs_sum<T><<<(unsigned)((m + 255) / 256), 256, 0, s>>>(R.part.as<cx<T>>(), R.zsplit, R.nbox, nr,
-                                                                         R.part_rhs, nrhs_max, blk,
-                                                                         (cx<T> *)A.lev[i - a].D);
+                const int l = Z.nset++;
+                Z.zsplit[l] = R.zsplit;
+                Z.part_rhs[l] = R.part_rhs;
+                Z.blk[l] = 3 * R.pd * R.pd;
+                Z.part[l] = R.part.p;
+                Z.D[l] = A.lev[i - a].D;
+                Z.first[l + 1] = Z.first[l] + R.nbox * nr * Z.blk[l];
+            }
+            if (Z.nset) {
+                k_rcs_sum<T><<<(unsigned)((Z.first[Z.nset] + 255) / 256), 256, 0, s>>>(Z);
                 FMB_LAUNCH_CHECK();
             }
         }

@@ -77,11 +77,6 @@ struct Mma<float> {
     __device__ static v4 mma(float a, float b, v4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 };
 
-// uniform data read through the scalar cache
-#define RCS_UNI __attribute__((address_space(4)))
-template <typename U>
-__device__ __forceinline__ const RCS_UNI U *rcs_uni(const U *p) { return (const RCS_UNI U *)p; }
-
 // x of the neighbouring column (re <-> im), with mask xored into its sign
 __device__ __forceinline__ float rcs_swap(float x, int mask) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, true) ^ mask);
@@ -242,8 +237,9 @@ __global__ void __launch_bounds__(WAVES * 64, MINW) k_rcs(RcsArgs A) {
         const int b = t / (NC * D2), e = t - b * NC * D2;
         acc[t] = V.accumulate ? Dg[b * dbox + e] : mk(T(0), T(0));
     }
-    const RCS_UNI int32_t *gc = rcs_uni(V.gcls + (int64_t)g * (V.ncls + 1));
-    const RCS_UNI int32_t *cdist = rcs_uni(V.cdist);
+    // class bounds and axial tables, a class per lane (ncls < 64)
+    const int bound = V.gcls[(int64_t)g * (V.ncls + 1) + min(lane, V.ncls)];
+    const int cdist = V.cdist[min(lane, V.ncls - 1)];
     // this thread's pair of a tile and its coefficients (n, +-m): opening and closing read and write the same LDS cells,
     // and a coefficient's sums stay within one wavefront
     const int j = tid & (RCS_TILE - 1);
@@ -265,13 +261,13 @@ __global__ void __launch_bounds__(WAVES * 64, MINW) k_rcs(RcsArgs A) {
     auto dn_of = [&](int i) { return up_[i] - 2 * (mn_[i] & 255); };
     auto at_of = [&](int i) { return up_[i] * 16 - (mn_[i] >> 8) + 2 * j; };
     // tiles: class by class, RCS_TILE pairs at a time; with zsplit every zsplit-th
-    int cls = 0, q = gc[0], qe = gc[1], skip = z;
+    int cls = 0, q = __builtin_amdgcn_readlane(bound, 0), qe = __builtin_amdgcn_readlane(bound, 1), skip = z;
     auto settle = [&]() {
         for (;;) {
             while (q >= qe && cls < V.ncls) {
                 if (++cls == V.ncls) return;
-                q = gc[cls];
-                qe = gc[cls + 1];
+                q = qe;
+                qe = __builtin_amdgcn_readlane(bound, cls + 1);
             }
             if (skip == 0) break;
             --skip;
@@ -287,7 +283,7 @@ __global__ void __launch_bounds__(WAVES * 64, MINW) k_rcs(RcsArgs A) {
         for (int i = 0; i < M.rmax; ++i) wf[i] = F[i * 64];
     };
     auto fetch_c = [&](int c) {
-        const T *F = (const T *)V.C + ((int64_t)(V.cdist ? cdist[c] : 0) * WAVES + wave) * M.smax * 64 + lane;
+        const T *F = (const T *)V.C + ((int64_t)__builtin_amdgcn_readlane(cdist, c) * WAVES + wave) * M.smax * 64 + lane;
 #pragma unroll
         for (int i = 0; i < M.smax; ++i) cf[i] = F[i * 64];
     };
@@ -307,7 +303,7 @@ __global__ void __launch_bounds__(WAVES * 64, MINW) k_rcs(RcsArgs A) {
             // phases, reflection and the even/odd combinations of the sources; columns past the last pair hold
             // whatever box 0 gives and are never read
             const C *src = (const C *)V.S + (((int64_t)en.x * A.nrhs_max + r) * 3 + ch) * S2;
-            const C *pj = (const C *)V.ph + (int64_t)(pair >> 12) * V.phs;
+            const C *pj = (const C *)V.ph + (int64_t)(pair >> 13) * V.phs;
             C f[IT], xu[IT][NC], xd[IT][NC];
 #pragma unroll
             for (int i = 0; i < IT; ++i)
@@ -363,7 +359,7 @@ __global__ void __launch_bounds__(WAVES * 64, MINW) k_rcs(RcsArgs A) {
         rcs_sync();
         // closing phases and sums; pairs of the tile that share a destination take turns, in list order
         renew();
-        const int turnof = (pair >> 9) & 7;
+        const int turnof = (pair >> 9) & 15;
         C *ac = acc + (pair & 255) * NC * D2;
         for (int k = 0;; ++k) {
             if (j < cnt && turnof == k) {
