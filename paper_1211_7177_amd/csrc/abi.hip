@@ -14,7 +14,7 @@ void set_error(const std::string &msg) { g_last_error = msg; }
 
 size_t Plan::device_bytes() const {
     size_t b = codes.bytes + perm.bytes + iperm.bytes + spts.bytes + snrm.bytes + sw.bytes + stri.bytes +
-               inv_alpha.bytes + btab.bytes + bgix.bytes + point_tri.bytes + unrm.bytes + tri_nodes.bytes + corr_v.bytes + corr_g.bytes +
+               inv_alpha.bytes + btab.bytes + lnode.bytes + point_tri.bytes + unrm.bytes + tri_nodes.bytes + corr_v.bytes + corr_g.bytes +
                src.bytes + ys.bytes + ybuf.bytes + hX1.bytes + hX2.bytes;
     for (const Level &V : lv)
         b += V.keys.bytes + V.start.bytes + V.parent.bytes + V.center.bytes + V.nbr.bytes + V.child_start.bytes +
@@ -185,6 +185,7 @@ int fmm_plan(const double *points, const double *normals, const double *weights,
             P.dense = dense_order(P.precision, P.translate_mode, order);
         }
         build_basis_tables(P, s);
+        if (P.far_on()) build_leaf_nodes(P, s);
         if (P.dense) {
             build_operators(P, s);
             build_tiles(P, s);

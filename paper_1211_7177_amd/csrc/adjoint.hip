@@ -50,110 +50,87 @@ __global__ void k_adj_gather(const cx<T> *__restrict__ y, const int32_t *__restr
 // Far field at the nodes of one leaf (blockIdx.x) for one right-hand side
 // (blockIdx.y): F_c = sum_nm L_nm,c R_n^m(s - X) and grad F_c.  The gradient
 // of a local expansion of degree < p is one of degree <= p: the plan's
-// gradient table gives grad R_n^{mu} as k times two terms per component
+// gradient table gives grad R_n^mu as k times two terms per component
 // (d_z, d_+ = d_x + i d_y, d_- = d_x - i d_y, each from R_{n+-1}) for mu = -m
-// at coefficient (n, m), so grad R_n^m is read from the row of (n, -m).  Per
-// channel the block scatters L into the three coefficient sets D_x, D_y, D_z
-// (one thread per set, fixed order), then every thread evaluates L and the
-// three sets at its nodes with one pass of the Legendre recurrence.
+// at coefficient (n, m).  Per channel the block gathers the coefficients of L, d_x L,
+// d_y L, d_z L from the degrees below and above (one thread per (n, +-m)) as the rows
+// of leaf_eval, and each wavefront evaluates 16 nodes on the matrix cores (8 of 16
+// columns).  One evaluation per node and lane took 2.2-2.4 ms for 60k nodes at order 23 in FP64.
 // out[(r n + i) 12 + e]: e = c for F_c, e = 3 + 3 i + c for d_i F_c.
-template <typename T>
-__global__ void __launch_bounds__(64) k_adj_l2p(const int32_t *__restrict__ start, const double *__restrict__ center,
-                                                const double *__restrict__ spts, int64_t n, int p, double k_re,
-                                                double k_im, const double *__restrict__ inv_alpha,
-                                                const T *__restrict__ tab, const int32_t *__restrict__ gix,
-                                                const int32_t *__restrict__ gath, int nrhs_max,
-                                                const cx<T> *__restrict__ Lc, cx<T> *__restrict__ out) {
+template <typename T, int TT>
+__global__ void __launch_bounds__(256) k_adj_l2p(const int32_t *__restrict__ start, const LeafNode<T> *__restrict__ geo,
+                                                 int64_t n, int p, double k_re, double k_im,
+                                                 const double *__restrict__ inv_alpha, const T *__restrict__ tab,
+                                                 int nrhs_max, const cx<T> *__restrict__ Lc, cx<T> *__restrict__ out) {
     extern __shared__ unsigned char smem[];
-    const int P2 = p * p, N = p, NN = (N + 1) * (N + 1), NS = NN + 1;
-    const BasisTab<T> bt = basis_tab(tab, gix, N, P2);
-    cx<T> *D = reinterpret_cast<cx<T> *>(smem);        // [4][NS]: L, D_x, D_y, D_z of one channel
-    cx<T> *jb = D + 4 * NS;                             // [blockDim][N + 1]
+    constexpr int CW = 8;
+    const int P2 = p * p, N = p, S = p + 1, NB = blockDim.x / 4;
+    const BasisTab<T> bt = basis_tab(tab, N);
+    cx<T> *inv = reinterpret_cast<cx<T> *>(smem);                       // [p+1]
+    cx<T> *lab = inv + p + 1;                                           // [p+2][S]
+    cx<T> *J = lab + (p + 2) * S;                                       // [p+1][NB]
+    cx<T> *Ls = J + (p + 1) * NB;                                       // [P2] one channel of L
+    cx<T> *rows = Ls + P2;                                              // [(p+1)(p+2) + 2][4]
+    T *qs = reinterpret_cast<T *>(rows + ((p + 1) * (p + 2) + 2) * 4);  // [S]
     const int box = blockIdx.x, r = blockIdx.y;
     const int s0 = start[box], s1 = start[box + 1];
-    const cx<T> k = mk((T)k_re, (T)k_im);
-    const double X[3] = {center[3 * box], center[3 * box + 1], center[3 * box + 2]};
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, kq = lane >> 4;
+    const cx<T> k = mk((T)k_re, (T)k_im), zero = mk(T(0), T(0));
     const cx<T> *Lb = Lc + ((int64_t)box * nrhs_max + r) * 3 * P2;
-    const int32_t *gptr = gath, *gent = gath + NN + 1;
-    for (int c = 0; c < 3; ++c) {
-        __syncthreads();                                // the previous channel's evaluation is done
-        for (int t = threadIdx.x; t < NS; t += blockDim.x) {
-            cx<T> v = mk(T(0), T(0));
-            if (t < P2) {
-                int nn = 0;
-                while ((nn + 1) * (nn + 1) <= t) ++nn;
-                v = (T)inv_alpha[nn] * Lb[c * P2 + t];
+    leaf_inv_table(p, inv);
+    leaf_tables(bt, N, lab, qs);
+    for (int t = threadIdx.x; t < 8; t += blockDim.x) rows[(p + 1) * (p + 2) * 4 + t] = zero;
+    for (int b0 = s0; b0 < s1; b0 += NB)
+        for (int c = 0; c < 3; ++c) {
+            leaf_sync();                                // the previous channel's evaluation is done
+            if (c == 0 && (int)threadIdx.x < NB)
+                leaf_bessel(geo[min(b0 + (int)threadIdx.x, s1 - 1)], p, N, inv, J + threadIdx.x, NB);
+            for (int t = threadIdx.x; t < P2; t += blockDim.x) {
+                int nn = (int)sqrtf((float)t);
+                if (nn * nn > t) --nn;
+                if ((nn + 1) * (nn + 1) <= t) ++nn;
+                Ls[t] = (T)inv_alpha[nn] * Lb[c * P2 + t];
             }
-            D[t] = v;
-        }
-        __syncthreads();
-        // D_x, D_y, D_z: every R-table entry o gathers the gradient terms that land on it, in increasing
-        // source index (the terms of coefficient idx: slots 0-1 d_z, 2-3 d_+, 4-5 d_- of its gradient row)
-        for (int o = threadIdx.x; o < NS; o += blockDim.x) {
-            cx<T> ax = mk(T(0), T(0)), ay = mk(T(0), T(0)), az = mk(T(0), T(0));
-            if (o < NN)
-                for (int e = gptr[o]; e < gptr[o + 1]; ++e) {
-                    const int pk = gent[e];
-                    const int idx = pk & 2047, row = (pk >> 11) & 2047, slot = pk >> 22;
-                    const T co = bt.gco[(int64_t)row * 6 + slot];
-                    const cx<T> l = k * D[idx];
-                    if (slot < 2) {
-                        az += co * l;                   // d_z
-                    } else {
-                        ax += co * (T(0.5) * l);        // d_x = (d_+ + d_-) / 2
-                        const cx<T> h = mk(T(0.5) * l.im, T(-0.5) * l.re);
-                        if (slot < 4) ay += co * h;     // d_y = (d_+ - d_-) / 2i
-                        else ay -= co * h;
-                    }
-                }
-            D[NS + o] = ax;
-            D[2 * NS + o] = ay;
-            D[3 * NS + o] = az;
-        }
-        __syncthreads();
-        for (int i = s0 + threadIdx.x; i < s1; i += blockDim.x) {
-            double d[3];
-            for (int q = 0; q < 3; ++q) d[q] = spts[3 * (int64_t)i + q] - X[q];
-            const double rr = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-            const double ir = rr > 0 ? 1.0 / rr : 0.0;
-            cx<T> *J = jb + threadIdx.x * (N + 1);
-            sph_bessel_j(mk((T)(k_re * rr), (T)(k_im * rr)), N, J);
-            const T x = rr > 0 ? (T)(d[2] * ir) : T(1);
-            const cx<T> w = mk((T)(d[0] * ir), (T)(d[1] * ir));
-            cx<T> acc[4] = {mk(T(0), T(0)), mk(T(0), T(0)), mk(T(0), T(0)), mk(T(0), T(0))};
-            cx<T> wm = mk(T(1), T(0));
-            for (int m = 0; m <= N; ++m) {
-                if (m > 0) wm = wm * w;
-                const T qmm = bt.qmm[m];
-                const T sgn = (m & 1) ? T(-1) : T(1);
-                T q2 = 0, q1 = qmm;
-                for (int nn = m; nn <= N; ++nn) {
-                    T qv;
-                    if (nn == m) qv = qmm;
-                    else if (nn == m + 1) qv = bt.q1[m] * x * qmm;
-                    else qv = bt.la[nn * (N + 1) + m] * (x * q1 - bt.lb[nn * (N + 1) + m] * q2);
-                    if (nn > m) {
-                        q2 = q1;
-                        q1 = qv;
-                    }
-                    const cx<T> Y = (sgn * qv) * wm;
-                    const cx<T> Rp = J[nn] * Y;
-                    const int ip = nn * nn + nn + m;
+            leaf_sync();
+            for (int t = threadIdx.x; t < (p + 1) * (p + 1); t += blockDim.x) {
+                int nn = (int)sqrtf((float)t);
+                if (nn * nn > t) --nn;
+                if ((nn + 1) * (nn + 1) <= t) ++nn;
+                const int m = t - nn * nn - nn;
+                if (m < 0) continue;
+                // co (k L) of source (ns, mu): its gradient row is (ns, -mu)
+                auto term = [&](int ns, int mu, int slot) {
+                    if (ns < 0 || ns >= p || mu > ns || -mu > ns) return zero;
+                    const int at = ns * ns + ns;
+                    return bt.gco[(at - mu) * 6 + slot] * (k * Ls[at + mu]);
+                };
+                cx<T> v[2][4];                          // orders m and -m: L, d_x, d_y, d_z
 #pragma unroll
-                    for (int s = 0; s < 4; ++s) acc[s] += D[s * NS + ip] * Rp;
-                    if (m > 0) {
-                        const cx<T> Rm = J[nn] * conj(Y);
-                        const int im = nn * nn + nn - m;
-#pragma unroll
-                        for (int s = 0; s < 4; ++s) acc[s] += D[s * NS + im] * Rm;
-                    }
+                for (int h = 0; h < 2; ++h) {
+                    const int mu = h ? -m : m;
+                    const cx<T> dp = term(nn - 1, mu - 1, 2) + term(nn + 1, mu - 1, 3);
+                    const cx<T> dm = term(nn - 1, mu + 1, 4) + term(nn + 1, mu + 1, 5);
+                    const cx<T> df = dp - dm;
+                    v[h][0] = nn < p ? Ls[nn * nn + nn + mu] : zero;
+                    v[h][1] = T(0.5) * (dp + dm);
+                    v[h][2] = mk(T(0.5) * df.im, T(-0.5) * df.re);
+                    v[h][3] = term(nn - 1, mu, 0) + term(nn + 1, mu, 1);
                 }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) leaf_rows(rows + (nn * (nn + 1) + 2 * m) * 4 + e, 4, m, v[0][e], v[1][e]);
             }
-            cx<T> *o = out + ((int64_t)r * n + i) * 12;
-            o[c] = acc[0];
-            for (int q = 0; q < 3; ++q) o[3 + 3 * q + c] = acc[1 + q];
+            leaf_sync();
+            const int t0 = b0 + 16 * wave;
+            if (t0 >= s1) continue;
+            const LeafNode<T> d = geo[min(t0 + col, s1 - 1)];
+            const auto o = leaf_eval<T, TT>(reinterpret_cast<const T *>(rows), CW, lab, S, qs, N, d.x, d.w, J + 16 * wave, NB);
+            const int set = col >> 1, e = set ? 3 * set + c : c;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = t0 + Mma16<T>::row(kq, q);
+                if (i < s1 && col < CW) reinterpret_cast<T *>(out + ((int64_t)r * n + i) * 12 + e)[col & 1] = o[q];
+            }
         }
-    }
 }
 
 // Near field of the adjoint: for each node beta of the leaf and every node
@@ -339,12 +316,6 @@ void gather_t(Plan &P, const void *y, int nrhs, hipStream_t s) {
     FMB_LAUNCH_CHECK();
 }
 
-size_t l2p_lds(const Plan &P, int threads) {
-    const size_t cs = P.precision == FMB_FP64 ? sizeof(cx<double>) : sizeof(cx<float>);
-    const int N = P.order, NS = (N + 1) * (N + 1) + 1;
-    return (size_t)(4 * NS + threads * (N + 1)) * cs;
-}
-
 template <typename T>
 __global__ void k_adj_zero(cx<T> *__restrict__ x, int64_t m) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -361,12 +332,18 @@ void l2p_t(Plan &P, int nrhs, hipStream_t s) {
         return;
     }
     const Level &LL = P.lv[P.depth];
-    const int threads = 64;
-    const size_t sh = l2p_lds(P, threads);
-    k_adj_l2p<T><<<dim3((unsigned)LL.nbox, (unsigned)nrhs), threads, sh, s>>>(
-        LL.start.as<int32_t>(), LL.center.as<double>(), P.spts.as<double>(), P.n, P.order, P.k_re, P.k_im,
-        P.inv_alpha.as<double>() + (size_t)P.depth * P.order, P.btab.as<T>(), P.bgix.as<int32_t>(),
-        P.agath.as<int32_t>(), P.nrhs_max, LL.L.as<cx<T>>(), P.aws.as<cx<T>>());
+    const int p = P.order;
+    // wavefronts for the nodes of an average leaf
+    const int waves = (int)std::min<int64_t>(4, std::max<int64_t>(1, (P.n + 16 * LL.nbox - 1) / (16 * LL.nbox)));
+    const size_t sh = (p + 1) * sizeof(T) + ((size_t)(p + 1) * (p + 3) + (size_t)(p + 1) * 16 * waves + (size_t)p * p +
+                                             ((size_t)(p + 1) * (p + 2) + 2) * 4) * sizeof(cx<T>);
+    auto kern = p < 8 ? k_adj_l2p<T, 4> : (p < 16 ? k_adj_l2p<T, 8> : (p < 24 ? k_adj_l2p<T, 12> : k_adj_l2p<T, 20>));
+    if (sh > 65536)
+        FMB_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                          (int)sh));
+    kern<<<dim3((unsigned)LL.nbox, (unsigned)nrhs), 64 * waves, sh, s>>>(
+        LL.start.as<int32_t>(), P.lnode.as<LeafNode<T>>(), P.n, p, P.k_re, P.k_im,
+        P.inv_alpha.as<double>() + (size_t)P.depth * p, P.btab.as<T>(), P.nrhs_max, LL.L.as<cx<T>>(), P.aws.as<cx<T>>());
     FMB_LAUNCH_CHECK();
 }
 
@@ -394,38 +371,11 @@ void finish_t(Plan &P, const void *y, void *abar, void *bbar, int nrhs, hipStrea
 }  // namespace
 
 void adjoint_prepare(Plan &P) {
-    FMB_REQUIRE(l2p_lds(P, 64) <= 65536, "the adjoint's far-field evaluation supports orders up to 23 in FP64");
     const size_t cs = P.precision == FMB_FP64 ? sizeof(cx<double>) : sizeof(cx<float>);
+    const size_t N1 = P.order + 1;
+    FMB_REQUIRE((4 * (N1 * N1 + 1) + 64 * N1) * cs <= 65536, "the adjoint's far-field evaluation supports orders up to 23 in FP64");
     const size_t need = (size_t)P.nrhs_max * P.n * 12 * cs;
     if (P.aws.bytes < need) P.aws.alloc(need);
-    if (!P.agath.p) {
-        // invert the gradient table: for every R-table entry o < (N+1)^2, the (source coefficient, its
-        // gradient row, slot) triples whose term lands on o, in increasing source coefficient
-        const int N = P.order, NN = (N + 1) * (N + 1), P2 = N * N;
-        std::vector<int32_t> gix((size_t)7 * P2);
-        FMB_CHECK_HIP(hipMemcpy(gix.data(), P.bgix.p, gix.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
-        std::vector<int32_t> ptr(NN + 1, 0), pos, ent;
-        std::vector<std::pair<int32_t, int32_t>> raw;
-        for (int idx = 0; idx < P2; ++idx) {
-            int nn = 0;
-            while ((nn + 1) * (nn + 1) <= idx) ++nn;
-            const int m = idx - nn * nn - nn, row = nn * nn + nn - m;
-            for (int slot = 0; slot < 6; ++slot) {
-                const int o = gix[(size_t)7 * row + slot];
-                if (o < 0 || o >= NN) continue;               // the zero entry (N+1)^2
-                raw.push_back({o, idx | (row << 11) | (slot << 22)});
-                ++ptr[o + 1];
-            }
-        }
-        for (int o = 0; o < NN; ++o) ptr[o + 1] += ptr[o];
-        pos.assign(ptr.begin(), ptr.end() - 1);
-        ent.resize(raw.size());
-        for (const auto &e : raw) ent[pos[e.first]++] = e.second;
-        std::vector<int32_t> buf(ptr);
-        buf.insert(buf.end(), ent.begin(), ent.end());
-        P.agath.alloc(buf.size() * sizeof(int32_t));
-        FMB_CHECK_HIP(hipMemcpy(P.agath.p, buf.data(), buf.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    }
 }
 
 void adjoint_gather(Plan &P, const void *y, int nrhs, hipStream_t s) {

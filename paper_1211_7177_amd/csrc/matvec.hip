@@ -75,209 +75,264 @@ __device__ inline int xcd_tile(int i, int ntiles) {
 }
 
 // ---------------------------------------------------------------- P2M
-// One block per leaf.  For a batch of the leaf's nodes the block first builds
-// the table R_n^m(s - X), n <= p, in LDS (one thread per (node, m) column;
-// entry (p+1)^2 of each node's table is a zero that stands for the terms the
-// gradient recurrence lacks), then G = blockDim / p^2 thread groups each take
-// every G-th node of the batch and accumulate all three channels of one
-// coefficient; the groups are summed in LDS at the end (fixed order, so the
-// result is deterministic).  The gradient of R_n^{-m} is
-//   d_z = k (c0 R[i0] + c1 R[i1]),  d_+ = k (c2 R[i2] + c3 R[i3]),  d_- = k (c4 R[i4] + c5 R[i5]),
-//   grad = ((d_+ + d_-) / 2, (d_+ - d_-) / 2i, d_z),
-// with coefficients and indices from the plan's table; k multiplies the whole
-// gradient part once per coefficient after the node loop.
-constexpr int P2M_SLOTS = 3;     // coefficients per thread when p^2 > blockDim (orders up to 27)
-constexpr int P2M_SLOTS_MAX = 7; // leaf orders 28..40 (7 x 256 >= 40^2)
-
-template <typename T, int SLOTS>
-__global__ void __launch_bounds__(TPB) k_p2m(const int32_t *__restrict__ start, const double *__restrict__ center,
-                                             const double *__restrict__ spts, const double *__restrict__ snrm,
-                                             const cx<T> *__restrict__ src, int64_t n, int p, double k_re, double k_im,
-                                             const double *__restrict__ inv_alpha, const T *__restrict__ tab,
-                                             const int32_t *__restrict__ gix, int nrhs, int nrhs_max, int batch,
-                                             cx<T> *__restrict__ M) {
+// One block per leaf and right-hand side, NG groups of 4 nodes at a time.  With W = n x a
+// the dipole part n (a . g) - a (n . g) - (n . a) g of a node is g x W - (n . a) g, so the
+// multipoles follow from the moments of seven complex densities (W, n . a, b) with
+// R_n^m, n <= p, and one gradient recurrence per coefficient instead of one per
+// coefficient and node.  The moments are a product on the matrix cores: wavefront t
+// owns the orders m = 8 t .. 8 t + 7 (16 rows: cos and sin), the columns are re and im
+// of the densities times j_n, the nodes are summed over.  The block walks the
+// degrees together: moments of degree n go to a ring of four degrees in LDS, then
+// the multipoles of degree n - 1 are formed from degrees n - 2 .. n:
+//   d_z = c0 Q[n+1, mu] + c1 Q[n-1, mu],  d_+- = c2|c4 Q[n+1, mu +- 1] + c3|c5 Q[n-1, mu +- 1],
+//   grad = k ((d_+ + d_-) / 2, (d_+ - d_-) / 2i, d_z),  mu = -m.
+// Leaves of more than 4 NG nodes add chunk by chunk.  Bound by latency: the degrees are a
+// serial chain of a short product, a barrier and a gradient step (a branch and its LDS latency per
+// group of 4 nodes cost 3/4 of the time before GS groups were loaded together).  One thread per
+// coefficient, gathering six table entries per node, took 5.7 ms for 753k nodes at order 17
+// in FP64 and 0.81 ms for 60k at 23, now 1.74 and 0.27; 4.2 ms for 3M at 12 in FP32, now 2.2.
+template <typename T, int NG>
+__global__ void __launch_bounds__(384, sizeof(T) == 8 ? 2 : (NG == 16 ? 3 : 4))
+    k_p2m(const int32_t *__restrict__ start, const LeafNode<T> *__restrict__ geo, const double *__restrict__ snrm,
+          const cx<T> *__restrict__ src, int64_t n, int p, double k_re, double k_im, const double *__restrict__ inv_alpha,
+          const T *__restrict__ tab, int nrhs_max, cx<T> *__restrict__ M) {
+    typedef typename Mma16<T>::v4 v4;
     extern __shared__ unsigned char smem[];
-    const int N = p;                                  // degrees 0..p for the gradients
-    const int NN = (N + 1) * (N + 1);
-    const int NT = NN + 1;                            // per-node table incl. the zero entry
-    const int P2 = p * p;
-    const BasisTab<T> bt = basis_tab(tab, gix, N, P2);
-    const int G = P2 <= (int)blockDim.x ? (int)blockDim.x / P2 : 1;   // node groups
-    const int grp = P2 <= (int)blockDim.x ? (int)threadIdx.x / P2 : 0;
-    cx<T> *red = reinterpret_cast<cx<T> *>(smem);                       // [G][P2][3] (G > 1)
-    cx<T> *Rb = red + (G > 1 ? G * P2 * 3 : 0);                         // [batch][NT]
-    cx<T> *jb = Rb + batch * NT;                                        // [batch][N+1]
-    cx<T> *sv = jb + batch * (N + 1);                                   // [batch][7] node densities
-    T *dd = reinterpret_cast<T *>(sv + batch * 7);                      // [batch][3] cos th, sin th e^{i ph}
-    T *nvs = dd + batch * 3;                                            // [batch][3] normals
-    const int box = blockIdx.x;
+    constexpr int NB = 4 * NG, GS = NG / 4;     // GS groups' loads ahead of their products
+    const int N = p, P2 = p * p, W2 = 2 * N + 1;
+    const BasisTab<T> bt = basis_tab(tab, N);
+    cx<T> *J = reinterpret_cast<cx<T> *>(smem);                         // [N+1][NB]
+    cx<T> *inv = J + (N + 1) * NB;                                      // [N+1]
+    cx<T> *sc = inv + N + 1;                                            // [p] i k / alpha_n
+    cx<T> *lab = sc + p;                                                // [N+1][N+1] la, lb (zero up to the diagonal)
+    T *V = reinterpret_cast<T *>(lab + (N + 1) * (N + 1));              // [NB][16] densities
+    T *xs = V + NB * 16;                                                // [NB] cos th
+    cx<T> *wp = reinterpret_cast<cx<T> *>(xs + NB);                     // [N+1][NB] powers of sin th e^{i ph}, then
+    cx<T> *ring = wp;                                                   // [4][W2][7] moments of four degrees
+    const int box = blockIdx.x, r = blockIdx.y;
     const int s0 = start[box], s1 = start[box + 1];
-    const double X[3] = {center[3 * box], center[3 * box + 1], center[3 * box + 2]};
     const cx<T> k = mk((T)k_re, (T)k_im);
-    // a leaf that fits one batch builds its tables once for all right-hand sides
-    const bool one = s1 - s0 <= batch;
-    for (int r = 0; r < nrhs; ++r) {
-        cx<T> accb[SLOTS][3], accg[SLOTS][3];
-        for (int u = 0; u < SLOTS; ++u)
-            for (int c = 0; c < 3; ++c) accb[u][c] = accg[u][c] = mk(T(0), T(0));
-        for (int b0 = s0; b0 < s1; b0 += batch) {
-            const int nb = min(batch, s1 - b0);
-            __syncthreads();
-            if (!one || r == 0) {
-                for (int t = threadIdx.x; t < nb; t += blockDim.x) {
-                    const int i = b0 + t;
-                    double d[3];
-                    for (int q = 0; q < 3; ++q) d[q] = spts[3 * (int64_t)i + q] - X[q];
-                    const double rr = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-                    const double ir = rr > 0 ? 1.0 / rr : 0.0;
-                    dd[t * 3] = rr > 0 ? (T)(d[2] * ir) : T(1);
-                    dd[t * 3 + 1] = (T)(d[0] * ir);
-                    dd[t * 3 + 2] = (T)(d[1] * ir);
-                    sph_bessel_j(mk((T)(k_re * rr), (T)(k_im * rr)), N, jb + t * (N + 1));
-                    Rb[t * NT + NN] = mk(T(0), T(0));
-                    for (int q = 0; q < 3; ++q) nvs[t * 3 + q] = (T)snrm[3 * (int64_t)i + q];
-                }
-                __syncthreads();
-                for (int t = threadIdx.x; t < nb * (N + 1); t += blockDim.x) {
-                    const int i = t / (N + 1), m = t % (N + 1);
-                    regular_column<T>(dd[3 * i], mk(dd[3 * i + 1], dd[3 * i + 2]), jb + i * (N + 1), bt, m,
-                                      Rb + i * NT);
-                }
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int kq = lane >> 4, col = lane & 15;
+    // the lane's row as input (order, cos | sin)
+    const int rq = Mma16<T>::q_of(col), rm = 8 * wave + 2 * Mma16<T>::kq_of(col) + (rq >> 1);
+    const int mc = min(rm, N);
+    const bool sine = rq & 1;
+    leaf_inv_table(N, inv);
+    for (int t = threadIdx.x; t < (N + 1) * (N + 1); t += blockDim.x) lab[t] = mk(bt.la[t], bt.lb[t]);
+    for (int t = threadIdx.x; t < p; t += blockDim.x) sc[t] = mk((T)(-k_im * inv_alpha[t]), (T)(k_re * inv_alpha[t]));
+    cx<T> *Mo = M + ((int64_t)box * nrhs_max + r) * 3 * P2;
+    if (s0 == s1)
+        for (int t = threadIdx.x; t < 3 * P2; t += blockDim.x) Mo[t] = mk(T(0), T(0));
+    for (int b0 = s0; b0 < s1; b0 += NB) {
+        const int nb = min(NB, s1 - b0);
+        leaf_sync();
+        for (int t = threadIdx.x; t < 2 * NB; t += blockDim.x) {
+            const int j = t % NB;
+            const int64_t i = b0 + min(j, nb - 1);
+            const LeafNode<T> d = geo[i];
+            if (t < NB) {
+                leaf_bessel(d, N, N, inv, J + j, NB);
+                continue;
             }
-            for (int t = threadIdx.x; t < nb * 7; t += blockDim.x)
-                sv[t] = src[((int64_t)r * n + b0) * 7 + t];
-            __syncthreads();
-            for (int u = 0; u < SLOTS; ++u) {
-                const int idx = (G > 1) ? ((int)threadIdx.x % P2) : (int)threadIdx.x + u * (int)blockDim.x;
-                if (idx >= P2 || grp >= G || (G > 1 && u > 0)) break;
-                int ix[7];
-                T co[6];
-                for (int q = 0; q < 7; ++q) ix[q] = bt.gix[idx * 7 + q];
-                for (int q = 0; q < 6; ++q) co[q] = bt.gco[idx * 6 + q];
-                for (int i = grp; i < nb; i += G) {
-                    const cx<T> *R = Rb + i * NT;
-                    const cx<T> Rv = R[ix[6]];                                  // R_n^{-m}
-                    const cx<T> dz = co[0] * R[ix[0]] + co[1] * R[ix[1]];
-                    const cx<T> dp = co[2] * R[ix[2]] + co[3] * R[ix[3]];
-                    const cx<T> dm = co[4] * R[ix[4]] + co[5] * R[ix[5]];
-                    const cx<T> df = dp - dm;
-                    const cx<T> g[3] = {T(0.5) * (dp + dm), mk(T(0.5) * df.im, T(-0.5) * df.re), dz};   // grad / k
-                    const cx<T> *sr = sv + i * 7;
-                    const T nv[3] = {nvs[3 * i], nvs[3 * i + 1], nvs[3 * i + 2]};
-                    const cx<T> aG = sr[0] * g[0] + sr[1] * g[1] + sr[2] * g[2];
-                    const cx<T> nG = nv[0] * g[0] + nv[1] * g[1] + nv[2] * g[2];
-                    for (int c = 0; c < 3; ++c) {
-                        accb[u][c] += sr[3 + c] * Rv;
-                        accg[u][c] += nv[c] * aG - sr[c] * nG - sr[6] * g[c];
+            xs[j] = d.x;
+            cx<T> wm = mk(T(1), T(0));
+            for (int m = 0; m <= N; ++m) {
+                wp[m * NB + j] = wm;
+                wm = wm * d.w;
+            }
+            cx<T> v[8];
+            for (int q = 0; q < 8; ++q) v[q] = mk(T(0), T(0));
+            if (j < nb) {
+                const cx<T> *sr = src + ((int64_t)r * n + i) * 7;
+                const T nv[3] = {(T)snrm[3 * i], (T)snrm[3 * i + 1], (T)snrm[3 * i + 2]};
+                const cx<T> a[3] = {sr[0], sr[1], sr[2]};
+                for (int c = 0; c < 3; ++c) {
+                    v[c] = nv[(c + 1) % 3] * a[(c + 2) % 3] - nv[(c + 2) % 3] * a[(c + 1) % 3];
+                    v[4 + c] = sr[3 + c];
+                }
+                v[3] = sr[6];
+            }
+            for (int q = 0; q < 8; ++q) *reinterpret_cast<cx<T> *>(V + j * 16 + 2 * q) = v[q];
+        }
+        leaf_sync();
+        // a lane holds its first value until degree m (rows of orders above the degree are not read)
+        T q1[NG], q2[NG], x[NG], v0[NG];
+        const T qs = (rm > N ? T(0) : T(1)) * ((mc & 1) ? -bt.qmm[mc] : bt.qmm[mc]);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const int j = 4 * g + kq;
+            const cx<T> wm = wp[mc * NB + j];
+            q1[g] = qs * (sine ? wm.im : wm.re);
+            q2[g] = T(0);
+            x[g] = xs[j];
+            v0[g] = V[j * 16 + col];
+        }
+        leaf_sync();
+        for (int nn = 0; nn <= N; ++nn) {
+            const int nm = nn - 1;
+            // gradient coefficients of the multipoles formed below: loaded ahead of the products
+            T co[6];
+#pragma unroll
+            for (int q = 0; q < 6; ++q) co[q] = bt.gco[min(max(nm, 0) * max(nm, 0) + lane, P2 - 1) * 6 + q];
+            cx<T> *rg = ring + (nn & 3) * 7 * W2;
+            // orders up to two beyond the degree are written as zeros: the recurrences read them
+            if (8 * wave <= nn + 2) {
+                const T la = lab[nn * (N + 1) + mc].re, lb = lab[nn * (N + 1) + mc].im;
+                const T hold = nn <= mc ? T(1) : T(0), neg = (col & 1) ? T(1) : T(-1);
+                const cx<T> *Jn = J + nn * NB + kq;
+                v4 acc = {0, 0, 0, 0}, acc2 = acc;
+                if (8 * wave <= nn) {
+#pragma unroll
+                    for (int g0 = 0; g0 < NG; g0 += GS)
+                        if (4 * g0 < nb) {
+                            cx<T> j[GS];
+#pragma unroll
+                            for (int g = 0; g < GS; ++g) j[g] = Jn[4 * (g0 + g)];
+#pragma unroll
+                            for (int g = 0; g < GS; ++g) {
+                                const T u = la * (x[g0 + g] * q1[g0 + g] - lb * q2[g0 + g]) + hold * q1[g0 + g];
+                                q2[g0 + g] = q1[g0 + g];
+                                q1[g0 + g] = u;
+                                const T d = j[g].re * v0[g0 + g] + (neg * j[g].im) * lane_swap(v0[g0 + g]);
+                                if (g & 1) acc2 = Mma16<T>::mma(u, d, acc2);
+                                else acc = Mma16<T>::mma(u, d, acc);
+                            }
+                        }
+                    acc += acc2;
+                }
+                // registers (0, 1) and (2, 3) are cos and sin of two orders
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int m = 8 * wave + 2 * kq + h;
+                    const T o = lane_swap(acc[2 * h + 1]), s = (col & 1) ? o : -o;
+                    if (m <= min(nn + 2, N) && col < 14) {
+                        T *at = reinterpret_cast<T *>(rg + 7 * N) + col;
+                        at[14 * m] = m <= nn ? acc[2 * h] + s : T(0);
+                        if (m) at[-14 * m] = m <= nn ? acc[2 * h] - s : T(0);
                     }
                 }
             }
-        }
-        cx<T> acc[SLOTS][3];
-        for (int u = 0; u < SLOTS; ++u)
-            for (int c = 0; c < 3; ++c) acc[u][c] = accb[u][c] + k * accg[u][c];
-        cx<T> *Mo = M + ((int64_t)box * nrhs_max + r) * 3 * P2;
-        if (G > 1) {
-            // sum the node groups in LDS
-            __syncthreads();
-            if (grp < G)
-                for (int c = 0; c < 3; ++c) red[(grp * P2 + (threadIdx.x % P2)) * 3 + c] = acc[0][c];
-            __syncthreads();
-            if ((int)threadIdx.x < P2) {
-                const int idx = threadIdx.x;
-                int nn = 0;
-                while ((nn + 1) * (nn + 1) <= idx) ++nn;
-                const cx<T> sc = mk((T)(-k_im * inv_alpha[nn]), (T)(k_re * inv_alpha[nn]));   // i k / alpha_n
-                for (int c = 0; c < 3; ++c) {
-                    cx<T> s = mk(T(0), T(0));
-                    for (int g2 = 0; g2 < G; ++g2) s += red[(g2 * P2 + idx) * 3 + c];
-                    Mo[c * P2 + idx] = sc * s;
+            leaf_sync();
+            if (nm < 0) continue;
+            // (degree -1 has zero coefficients: any finite values serve)
+            const cx<T> *up0 = rg + 7 * N, *dn0 = (nm ? ring + ((nn + 2) & 3) * 7 * W2 : rg) + 7 * N;
+            const cx<T> *mid0 = ring + ((nn + 3) & 3) * 7 * W2 + 7 * N;
+            for (int e = lane; e <= 2 * nm; e += 64) {
+                const int mu = nm - e, idx = nm * nm + e;
+                if (e >= 64)
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) co[q] = bt.gco[idx * 6 + q];
+                const cx<T> *up = up0 + 7 * mu, *dn = dn0 + 7 * mu;
+                auto dz = [&](int v) { return co[0] * up[v] + co[1] * dn[v]; };
+                auto dp = [&](int v) { return co[2] * up[7 + v] + co[3] * dn[7 + v]; };
+                auto dm = [&](int v) { return co[4] * up[v - 7] + co[5] * dn[v - 7]; };
+                auto dx = [&](int v) { return T(0.5) * (dp(v) + dm(v)); };
+                auto dy = [&](int v) {
+                    const cx<T> df = dp(v) - dm(v);
+                    return mk(T(0.5) * df.im, T(-0.5) * df.re);
+                };
+                for (int c = wave; c < 3; c += nw) {
+                    cx<T> gr;
+                    if (c == 0) gr = dy(2) - dz(1) - dx(3);
+                    else if (c == 1) gr = dz(0) - dx(2) - dy(3);
+                    else gr = dx(1) - dy(0) - dz(3);
+                    const cx<T> m = sc[nm] * (mid0[7 * mu + 4 + c] + k * gr);
+                    cx<T> *o = Mo + c * P2 + idx;
+                    *o = b0 == s0 ? m : *o + m;
                 }
-            }
-        } else {
-            for (int u = 0; u < SLOTS; ++u) {
-                const int idx = threadIdx.x + u * blockDim.x;
-                if (idx >= P2) break;
-                int nn = 0;
-                while ((nn + 1) * (nn + 1) <= idx) ++nn;
-                const cx<T> sc = mk((T)(-k_im * inv_alpha[nn]), (T)(k_re * inv_alpha[nn]));   // i k / alpha_n
-                for (int c = 0; c < 3; ++c) Mo[c * P2 + idx] = sc * acc[u][c];
             }
         }
     }
 }
 
+template <typename T, int NG>
+size_t p2m_lds(int N) {
+    return ((size_t)(N + 1) * 4 * NG + 2 * N + 1 + (size_t)(N + 1) * (N + 1)) * sizeof(cx<T>) +
+           (size_t)4 * NG * 17 * sizeof(T) +
+           std::max((size_t)(N + 1) * 4 * NG, (size_t)28 * (2 * N + 1)) * sizeof(cx<T>);
+}
+
 // ---------------------------------------------------------------- L2P
-// RC right-hand sides per block (blockIdx.y = chunk of RC): each node's basis
-// values are evaluated once and contracted with the RC local expansions.
-template <typename T, int RC>
-__global__ void __launch_bounds__(64) k_l2p(const int32_t *__restrict__ start, const double *__restrict__ center,
-                                            const double *__restrict__ spts, int64_t n, int p, double k_re, double k_im,
-                                            const double *__restrict__ inv_alpha, const T *__restrict__ tab,
-                                            int nrhs, int nrhs_max, const cx<T> *__restrict__ Lc,
-                                            cx<T> *__restrict__ ys) {
+// One block per leaf and RC right-hand sides, 16 nodes per wavefront at a time: the
+// coefficients are laid out once per block as the rows that leaf_eval multiplies
+// (6 RC of 16 columns: re and im of three channels), j_n of 16 nodes per wavefront
+// and the recurrence constants beside them.  One lane per node took 1.3 ms for 753k nodes at order 17
+// in FP64 and 0.52 ms for 60k at 23, now 0.56 and 0.17; loading two or four steps ahead does
+// work for absent orders and was slower (0.58, 0.80 ms).
+template <typename T, int RC, int TT>
+__global__ void __launch_bounds__(256) k_l2p(const int32_t *__restrict__ start, const LeafNode<T> *__restrict__ geo,
+                                            int64_t n, int p, const double *__restrict__ inv_alpha,
+                                            const T *__restrict__ tab, int nrhs, int nrhs_max,
+                                            const cx<T> *__restrict__ Lc, cx<T> *__restrict__ ys) {
     extern __shared__ unsigned char smem[];
-    const int P2 = p * p;
-    const BasisTab<T> bt = basis_tab(tab, (const int32_t *)nullptr, p, P2);
-    cx<T> *Ls = reinterpret_cast<cx<T> *>(smem);        // [RC][3][P2]
-    cx<T> *jb = Ls + RC * 3 * P2;                        // [64][p]
+    constexpr int CW = 6 * RC;
+    const int P2 = p * p, N = p - 1, S = p + 1, NB = blockDim.x / 4;
+    const BasisTab<T> bt = basis_tab(tab, p);
+    cx<T> *inv = reinterpret_cast<cx<T> *>(smem);                       // [p+1]
+    cx<T> *lab = inv + p + 1;                                           // [p+1][S]
+    cx<T> *J = lab + (p + 1) * S;                                       // [p][NB]
+    cx<T> *rows = J + p * NB;                                           // [p (p+1) + 2][CW / 2]
+    T *qs = reinterpret_cast<T *>(rows + (p * (p + 1) + 2) * (CW / 2)); // [S]
     const int box = blockIdx.x, r0 = blockIdx.y * RC;
     const int rcn = min(RC, nrhs - r0);
     const int s0 = start[box], s1 = start[box + 1];
-    for (int t = threadIdx.x; t < RC * 3 * P2; t += blockDim.x) {
-        const int rr = t / (3 * P2), e = t % (3 * P2);
-        const int idx = e % P2;
-        int nn = 0;
-        while ((nn + 1) * (nn + 1) <= idx) ++nn;
-        Ls[t] = rr < rcn ? (T)inv_alpha[nn] * Lc[((int64_t)box * nrhs_max + r0 + rr) * 3 * P2 + e] : mk(T(0), T(0));
-    }
-    __syncthreads();
-    const double X[3] = {center[3 * box], center[3 * box + 1], center[3 * box + 2]};
-    for (int i = s0 + threadIdx.x; i < s1; i += blockDim.x) {
-        double d[3];
-        for (int q = 0; q < 3; ++q) d[q] = spts[3 * (int64_t)i + q] - X[q];
-        const double rr = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-        const double ir = rr > 0 ? 1.0 / rr : 0.0;
-        cx<T> *J = jb + threadIdx.x * p;
-        sph_bessel_j(mk((T)(k_re * rr), (T)(k_im * rr)), p - 1, J);
-        const T x = rr > 0 ? (T)(d[2] * ir) : T(1);
-        const cx<T> w = mk((T)(d[0] * ir), (T)(d[1] * ir));
-        cx<T> acc[RC][3];
-#pragma unroll
-        for (int q = 0; q < RC; ++q)
-            for (int c = 0; c < 3; ++c) acc[q][c] = mk(T(0), T(0));
-        cx<T> wm = mk(T(1), T(0));
-        for (int m = 0; m < p; ++m) {
-            if (m > 0) wm = wm * w;
-            const T qmm = bt.qmm[m];
-            const T sgn = (m & 1) ? T(-1) : T(1);
-            T q2 = 0, q1 = qmm;
-            for (int nn = m; nn < p; ++nn) {
-                T q;
-                if (nn == m) q = qmm;
-                else if (nn == m + 1) q = bt.q1[m] * x * qmm;
-                else q = bt.la[nn * (bt.N + 1) + m] * (x * q1 - bt.lb[nn * (bt.N + 1) + m] * q2);
-                if (nn > m) {
-                    q2 = q1;
-                    q1 = q;
-                }
-                const cx<T> Y = (sgn * q) * wm;
-                const cx<T> Rp = J[nn] * Y;
-                const cx<T> Rm = J[nn] * conj(Y);
-#pragma unroll
-                for (int rq = 0; rq < RC; ++rq) {
-                    const cx<T> *L = Ls + rq * 3 * P2;
-                    for (int c = 0; c < 3; ++c) acc[rq][c] += L[c * P2 + nn * nn + nn + m] * Rp;
-                    if (m > 0)
-                        for (int c = 0; c < 3; ++c) acc[rq][c] += L[c * P2 + nn * nn + nn - m] * Rm;
-                }
+    leaf_inv_table(p, inv);
+    leaf_tables(bt, N, lab, qs);
+    for (int t = threadIdx.x; t < 2 * (CW / 2); t += blockDim.x) rows[p * (p + 1) * (CW / 2) + t] = mk(T(0), T(0));
+    for (int idx = threadIdx.x; idx < P2; idx += blockDim.x) {
+        int nn = (int)sqrtf((float)idx);
+        if (nn * nn > idx) --nn;
+        if ((nn + 1) * (nn + 1) <= idx) ++nn;
+        const int m = idx - nn * nn - nn;
+        if (m < 0) continue;
+        const T ia = (T)inv_alpha[nn];
+        cx<T> *o = rows + (nn * (nn + 1) + 2 * m) * (CW / 2);
+        for (int e = 0; e < 3 * RC; ++e) {
+            cx<T> a = mk(T(0), T(0)), b = a;
+            if (e / 3 < rcn) {
+                const cx<T> *L = Lc + (((int64_t)box * nrhs_max + r0) * 3 + e) * P2 + idx;
+                a = ia * L[0];
+                b = ia * L[-2 * m];
             }
+            leaf_rows(o + e, CW / 2, m, a, b);
         }
-#pragma unroll
-        for (int rq = 0; rq < RC; ++rq)
-            if (rq < rcn)
-                for (int c = 0; c < 3; ++c) ys[((int64_t)(r0 + rq) * n + i) * 3 + c] = acc[rq][c];
     }
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, kq = lane >> 4;
+    for (int b0 = s0; b0 < s1; b0 += NB) {
+        leaf_sync();
+        if ((int)threadIdx.x < NB)
+            leaf_bessel(geo[min(b0 + (int)threadIdx.x, s1 - 1)], p, N, inv, J + threadIdx.x, NB);
+        leaf_sync();
+        const int t0 = b0 + 16 * wave;
+        if (t0 >= s1) continue;
+        const LeafNode<T> d = geo[min(t0 + col, s1 - 1)];
+        const auto o = leaf_eval<T, TT>(reinterpret_cast<const T *>(rows), CW, lab, S, qs, N, d.x, d.w, J + 16 * wave, NB);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int i = t0 + Mma16<T>::row(kq, q);
+            if (i < s1 && col < 6 * rcn)
+                reinterpret_cast<T *>(ys + ((int64_t)(r0 + col / 6) * n + i) * 3)[col % 6] = o[q];
+        }
+    }
+}
+
+template <typename T, int RC>
+void launch_l2p(Plan &P, int nrhs, const cx<T> *Lc, cx<T> *ys, hipStream_t s) {
+    const int p = P.order;
+    const Level &LL = P.lv[P.depth];
+    // wavefronts for the nodes of an average leaf
+    const int waves = (int)std::min<int64_t>(4, std::max<int64_t>(1, (P.n + 16 * LL.nbox - 1) / (16 * LL.nbox)));
+    const size_t sh = (p + 1) * sizeof(T) +
+                      ((size_t)(p + 1) * (p + 2) + (size_t)p * 16 * waves + (size_t)(p * (p + 1) + 2) * 3 * RC) * sizeof(cx<T>);
+    auto kern = p <= 8 ? k_l2p<T, RC, 4> : (p <= 16 ? k_l2p<T, RC, 8> : (p <= 24 ? k_l2p<T, RC, 12> : k_l2p<T, RC, 20>));
+    if (sh > 65536)
+        FMB_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                          (int)sh));
+    kern<<<dim3((unsigned)LL.nbox, (unsigned)((nrhs + RC - 1) / RC)), 64 * waves, sh, s>>>(
+        LL.start.as<int32_t>(), P.lnode.as<LeafNode<T>>(), P.n, p, P.inv_alpha.as<double>() + (size_t)P.depth * p,
+        P.btab.as<T>(), nrhs, P.nrhs_max, Lc, ys);
+    FMB_LAUNCH_CHECK();
 }
 
 // ---------------------------------------------------------------- P2P
@@ -1136,24 +1191,18 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
     const int lmin = std::max(2, P.far_lmin);
     if (step == k++) {
         if (!far) return true;
-        const int N = p;
-        const size_t per = ((size_t)(N + 1) * (N + 2) + 1 + 7) * sizeof(cx<T>) + 6 * sizeof(T);
-        // LDS: the group-reduction area (G * P2 * 3 complex when G > 1), then per node of a batch
-        const int G = P2 <= TPB ? TPB / P2 : 1;
-        const size_t redb = G > 1 ? (size_t)G * P2 * 3 * sizeof(cx<T>) : 0;
-        // node batches sized so that the block's LDS stays near 24 KB (several blocks share a CU), with at
-        // least 8 nodes per batch while 60 KB allow it
-        const size_t fit = (60000 - redb) / per;
-        const size_t want = std::max<size_t>(8, (redb < 24000 ? 24000 - redb : 0) / per);
-        const int batch = (int)std::max<size_t>(1, std::min<size_t>({(size_t)64, fit, want}));
-        const size_t sh = redb + (size_t)batch * per;
-        FMB_REQUIRE(P2 <= P2M_SLOTS_MAX * TPB, "leaf order too large for the multipole kernel");
-        auto kern = P2 <= P2M_SLOTS * TPB ? k_p2m<T, P2M_SLOTS> : k_p2m<T, P2M_SLOTS_MAX>;
+        FMB_REQUIRE(p <= 40, "leaf order too large for the multipole kernel");
+        // chunks of 64 nodes when a leaf has more than 32 on average and two blocks' tables fit a CU
+        const bool wide = P.n > 32 * LL.nbox && p2m_lds<T, 16>(p) <= 80 * 1024;
+        auto kern = wide ? k_p2m<T, 16> : k_p2m<T, 8>;
+        const size_t sh = wide ? p2m_lds<T, 16>(p) : p2m_lds<T, 8>(p);
+        if (sh > 65536)
+            FMB_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
         tm.begin(ST_P2M, s, ev);
-        kern<<<(unsigned)LL.nbox, TPB, sh, s>>>(
-            LL.start.as<int32_t>(), LL.center.as<double>(), P.spts.as<double>(), P.snrm.as<double>(), src, n, p, P.k_re,
-            P.k_im, P.inv_alpha.as<double>() + (size_t)L * p, P.btab.as<T>(), P.bgix.as<int32_t>(), nrhs, P.nrhs_max,
-            batch, LL.M.as<cx<T>>());
+        kern<<<dim3((unsigned)LL.nbox, (unsigned)nrhs), 64 * (p / 8 + 1), sh, s>>>(
+            LL.start.as<int32_t>(), P.lnode.as<LeafNode<T>>(), P.snrm.as<double>(), src, n, p, P.k_re, P.k_im,
+            P.inv_alpha.as<double>() + (size_t)L * p, P.btab.as<T>(), P.nrhs_max, LL.M.as<cx<T>>());
         FMB_LAUNCH_CHECK();
         tm.end(ST_P2M, s, ev);
         return true;
@@ -1268,17 +1317,9 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
             FMB_LAUNCH_CHECK();
             return true;
         }
-        // chunk of right-hand sides per block while their local expansions fit ~24 KB of LDS
-        const size_t lrhs = (size_t)3 * P2 * sizeof(cx<T>);
-        const int rc = (nrhs >= 8 && 8 * lrhs <= 24576) ? 8 : ((nrhs >= 4 && 4 * lrhs <= 24576) ? 4 : 1);
-        const size_t sh = (size_t)rc * lrhs + (size_t)64 * p * sizeof(cx<T>);
-        const dim3 grid((unsigned)LL.nbox, (unsigned)((nrhs + rc - 1) / rc));
-        auto kern = rc == 8 ? k_l2p<T, 8> : (rc == 4 ? k_l2p<T, 4> : k_l2p<T, 1>);
         tm.begin(ST_L2P, s, ev);
-        kern<<<grid, 64, sh, s>>>(LL.start.as<int32_t>(), LL.center.as<double>(), P.spts.as<double>(), n, p, P.k_re,
-                                  P.k_im, P.inv_alpha.as<double>() + (size_t)L * p, P.btab.as<T>(), nrhs, P.nrhs_max,
-                                  LL.L.as<cx<T>>(), ys);
-        FMB_LAUNCH_CHECK();
+        if (nrhs > 1) launch_l2p<T, 2>(P, nrhs, LL.L.as<cx<T>>(), ys, s);
+        else launch_l2p<T, 1>(P, nrhs, LL.L.as<cx<T>>(), ys, s);
         tm.end(ST_L2P, s, ev);
         return true;
     }

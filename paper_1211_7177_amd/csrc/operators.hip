@@ -20,6 +20,7 @@
 // library stores Mtilde_n = M_n / alpha_n(l) and Ltilde_n = L_n alpha_n(l) with
 // alpha_n(l) = |j_n(i |k| rho_l)| (modified spherical Bessel i_n), rho_l the
 // radius of a level-l box.  The operators built here include these factors.
+#include "basis.h"
 #include "plan.h"
 
 namespace fmb {
@@ -225,6 +226,51 @@ __global__ void k_build_op(OpDesc const *__restrict__ descs, int p, double k_re,
     }
 }
 
+// Head of a node's Bessel recurrence, in FP64: downward from far above p as in sph_bessel_j, from
+// g_{n+1} = g_n = 1; the scale comes from j_0 or j_1, whichever is larger.
+template <typename T>
+__global__ void k_leaf_nodes(const int32_t *__restrict__ start, const double *__restrict__ center,
+                             const double *__restrict__ spts, int p, double k_re, double k_im,
+                             LeafNode<T> *__restrict__ out) {
+    const int box = blockIdx.x;
+    for (int i = start[box] + threadIdx.x; i < start[box + 1]; i += blockDim.x) {
+        double d[3];
+        for (int q = 0; q < 3; ++q) d[q] = spts[3 * (int64_t)i + q] - center[3 * box + q];
+        const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+        const double ir = r > 0 ? 1.0 / r : 0.0;
+        const cx<double> z = mk(k_re * r, k_im * r), z2 = z * z;
+        const double az = sqrt(abs2(z));
+        cx<double> g1 = mk(1.0, 0.0), g = mk(1.0, 0.0), h0 = g, h1 = g;
+        for (int n = p + 16 + (int)(1.2 * az); n >= 1; --n) {
+            if (n == p) {
+                h0 = g;
+                h1 = g1;
+            }
+            const cx<double> h = g - (1.0 / ((2.0 * n + 1.0) * (2.0 * n + 3.0)) * z2) * g1;
+            g1 = g;
+            g = h;
+        }
+        cx<double> sc;
+        if (az < 1e-3) {
+            sc = cdiv(mk(1.0, 0.0) - z2 * (1.0 / 6.0) + (z2 * z2) * (1.0 / 120.0), g);
+        } else {
+            const cx<double> sn = csin_(z), cs = mk(cos(z.re) * cosh(z.im), -sin(z.re) * sinh(z.im));
+            const cx<double> j0 = cdiv(sn, z), j1 = cdiv(j0 - cs, z);
+            sc = az > 1.0 && abs2(j1) > abs2(j0) ? cdiv(3.0 * j1, z * g1) : cdiv(j0, g);
+        }
+        h0 = sc * h0;
+        h1 = sc * h1;
+        LeafNode<T> o;
+        o.x = r > 0 ? (T)(d[2] * ir) : T(1);
+        o.pad = T(0);
+        o.w = mk((T)(d[0] * ir), (T)(d[1] * ir));
+        o.z = mk((T)z.re, (T)z.im);
+        o.g0 = mk((T)h0.re, (T)h0.im);
+        o.g1 = mk((T)h1.re, (T)h1.im);
+        out[i] = o;
+    }
+}
+
 }  // namespace
 
 // Recurrence constants for the basis kernels (P2M, L2P), N = order:
@@ -242,15 +288,13 @@ void build_basis_tables(Plan &P, hipStream_t s) {
     std::vector<double> t((size_t)2 * NN + 2 * (N + 1) + (size_t)6 * P2, 0.0);
     double *la = t.data(), *lb = la + NN, *qmm = lb + NN, *q1 = qmm + (N + 1), *gco = q1 + (N + 1);
     for (int m = 0; m <= N; ++m)
-        for (int n = m + 2; n <= N; ++n) {
+        for (int n = m + 1; n <= N; ++n) {
             la[n * (N + 1) + m] = std::sqrt((4.0 * n * n - 1.0) / ((double)n * n - (double)m * m));
             lb[n * (N + 1) + m] = std::sqrt(((double)(n - 1) * (n - 1) - (double)m * m) / (4.0 * (n - 1) * (n - 1) - 1.0));
         }
     qmm[0] = 0.28209479177387814347;
     for (int m = 1; m <= N; ++m) qmm[m] = qmm[m - 1] * std::sqrt((2.0 * m + 1.0) / (2.0 * m));
     for (int m = 0; m <= N; ++m) q1[m] = std::sqrt(2.0 * m + 3.0);
-    std::vector<int32_t> gix((size_t)7 * P2);
-    auto at = [&](int n, int mu) { return (n < 0 || n > N || mu > n || mu < -n) ? NN : n * n + n + mu; };
     for (int idx = 0; idx < P2; ++idx) {
         int n = 0;
         while ((n + 1) * (n + 1) <= idx) ++n;
@@ -274,14 +318,6 @@ void build_basis_tables(Plan &P, hipStream_t s) {
         g[3] = su * d;
         g[4] = -sd * e;
         g[5] = sd * f;
-        int32_t *ix = gix.data() + (size_t)7 * idx;
-        ix[0] = at(n + 1, mu);
-        ix[1] = at(n - 1, mu);
-        ix[2] = at(n + 1, mu + 1);
-        ix[3] = at(n - 1, mu + 1);
-        ix[4] = at(n + 1, mu - 1);
-        ix[5] = at(n - 1, mu - 1);
-        ix[6] = at(n, mu);
     }
     if (P.precision == FMB_FP64) {
         P.btab.alloc(t.size() * sizeof(double));
@@ -291,9 +327,20 @@ void build_basis_tables(Plan &P, hipStream_t s) {
         P.btab.alloc(tf.size() * sizeof(float));
         FMB_CHECK_HIP(hipMemcpyAsync(P.btab.p, tf.data(), tf.size() * sizeof(float), hipMemcpyHostToDevice, s));
     }
-    P.bgix.alloc(gix.size() * sizeof(int32_t));
-    FMB_CHECK_HIP(hipMemcpyAsync(P.bgix.p, gix.data(), gix.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
     FMB_CHECK_HIP(hipStreamSynchronize(s));
+}
+
+void build_leaf_nodes(Plan &P, hipStream_t s) {
+    const Level &LL = P.lv[P.depth];
+    const bool f64 = P.precision == FMB_FP64;
+    P.lnode.alloc((size_t)P.n * (f64 ? sizeof(LeafNode<double>) : sizeof(LeafNode<float>)));
+    auto fill = [&](auto kern, auto *out) {
+        kern<<<(unsigned)LL.nbox, 64, 0, s>>>(LL.start.as<int32_t>(), LL.center.as<double>(), P.spts.as<double>(), P.order,
+                                              P.k_re, P.k_im, out);
+        FMB_LAUNCH_CHECK();
+    };
+    if (f64) fill(k_leaf_nodes<double>, P.lnode.as<LeafNode<double>>());
+    else fill(k_leaf_nodes<float>, P.lnode.as<LeafNode<float>>());
 }
 
 void build_operators(Plan &P, hipStream_t s) {

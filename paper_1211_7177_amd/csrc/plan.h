@@ -117,7 +117,7 @@ struct Plan {
     DevBuf stri;      // i32[n]
     DevBuf inv_alpha; // f64[depth+1][order] 1/alpha_n per level
     DevBuf btab;      // basis recurrence constants in the plan's precision (BasisTab layout, N = order)
-    DevBuf bgix;      // i32[order^2][7] R-table indices of the gradient terms
+    DevBuf lnode;     // LeafNode[n] in the plan's precision, Morton order (plans with a far field)
     // corrections (user order)
     DevBuf point_tri; // i32[n]
     DevBuf unrm;      // f64[n][3] normals, user order
@@ -129,7 +129,6 @@ struct Plan {
     DevBuf ys;        // [nrhs_max][n][3] complex, Morton order
     DevBuf ybuf;      // GEMM output slots, largest level
     DevBuf aws;       // adjoint: [nrhs_max][n][12] potentials and gradients per channel, Morton order (on first use)
-    DevBuf agath;     // adjoint: per R-table entry, the gradient terms that land on it (on first use)
     StageTimer timer;
     size_t device_bytes() const;
 };
@@ -143,6 +142,7 @@ void gather_nodes(Plan &P, const double *d_pts, const double *d_nrm, const doubl
                   hipStream_t s);
 void build_operators(Plan &P, hipStream_t s);
 void build_basis_tables(Plan &P, hipStream_t s);
+void build_leaf_nodes(Plan &P, hipStream_t s);
 // rotation / coaxial translations (hf.hip)
 int hf_order(double kabs, double side, double tol);
 void build_hf(Plan &P, hipStream_t s);
