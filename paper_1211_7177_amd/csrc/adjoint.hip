@@ -151,10 +151,14 @@ __global__ void __launch_bounds__(ATPB) k_adj_p2p(const int32_t *__restrict__ st
                                                   const double *__restrict__ spts, const int32_t *__restrict__ stri,
                                                   const cx<T> *__restrict__ src, int64_t n, double k_re, double k_im,
                                                   double rcut2, cx<T> *__restrict__ out) {
-    __shared__ AdjTile<T> tile;
+    __shared__ union {
+        AdjTile<T> tile;
+        cx<T> red[ATPB][12];
+    } sh;
+    auto &tile = sh.tile;
+    auto &red = sh.red;
     __shared__ int32_t nb_start[28], nb_box[27];
     __shared__ int n_nb;
-    __shared__ cx<T> red[ATPB][12];
     const int box = blockIdx.x, r = blockIdx.y;
     const int t0 = start[box], t1 = start[box + 1];
     const int nt = t1 - t0;
@@ -238,6 +242,7 @@ __global__ void __launch_bounds__(ATPB) k_adj_p2p(const int32_t *__restrict__ st
                 o[e] += s;
             }
         }
+        __syncthreads();
     }
 }
 
