@@ -460,10 +460,11 @@ __global__ void __launch_bounds__(TPB, 4)
 // to different XCDs; giving each XCD contiguous runs of leaves cuts the L2-miss
 // traffic (52 -> 12 MB per launch on the 60k-node torus) but unbalances the
 // load and is slower, and the kernel is bound by its arithmetic.  Source
-// records are packed into six 16-byte LDS words per source: position relative
+// records are packed into five 16-byte LDS words per source: position relative
 // to the target leaf's centre (FP32; the leaf and its neighbours span a few
 // leaf widths, so the difference keeps FP32 relative accuracy) with the
-// triangle id, the normal, and the seven density values.  The transcendentals
+// triangle id, and seven density values: W = n x a formed once per source (the
+// dipole part n (d . a) - a (d . n) - d (n . a) is d x W - d (n . a)), b and n . a.  The transcendentals
 // go straight to the hardware units with the scale folded into the constants:
 // v_sin/v_cos take revolutions (kR / 2 pi), v_exp takes a base-2 exponent
 // (-Im k R log2 e); the LOSSY = false instance (real k) skips the decay
@@ -478,6 +479,18 @@ struct __attribute__((aligned(16))) SrcHdr32 {
 // RC right-hand sides per block (blockIdx.y = chunk of RC): the pair geometry,
 // the transcendentals and g, f are computed once per pair and applied to all
 // RC density sets.  The source tile shrinks as RC grows to keep LDS near 32 KB.
+// word pair w of a staged record: (W_w, b_w) for w < 3, n . a for w = 3
+__device__ __forceinline__ void stage_rec32(const SrcHdr32 &h, const cx<float> *__restrict__ sr, int w, cx<float> *rec) {
+    if (w == 3) {
+        rec[6] = sr[6];
+        return;
+    }
+    const int u = w == 2 ? 0 : w + 1, v = w == 0 ? 2 : w - 1;
+    const float n1 = w == 0 ? h.ny : (w == 1 ? h.nz : h.nx), n2 = w == 0 ? h.nz : (w == 1 ? h.nx : h.ny);
+    rec[w] = n1 * sr[v] - n2 * sr[u];
+    rec[3 + w] = sr[3 + w];
+}
+
 template <int RC>
 struct P2PTile {
     static constexpr int TS = RC == 1 ? 256 : (RC == 2 ? 128 : 64);
@@ -492,7 +505,7 @@ __global__ void __launch_bounds__(TPB) k_p2p32(int nleaf, int nrhs, const int32_
                                                double k_im, float rcut2, cx<float> *__restrict__ ys) {
     constexpr int TS = P2PTile<RC>::TS;
     __shared__ SrcHdr32 hdr[TS];
-    __shared__ __attribute__((aligned(16))) cx<float> rec[TS][RC][8];   // a[3], b[3], n.a, unused
+    __shared__ __attribute__((aligned(16))) cx<float> rec[TS][RC][8];   // n x a, b, n.a, unused
     __shared__ int32_t sid[TS];
     __shared__ int32_t nb_start[28], nb_box[27];
     __shared__ int n_nb;
@@ -562,9 +575,10 @@ __global__ void __launch_bounds__(TPB) k_p2p32(int nleaf, int nrhs, const int32_
                 sid[j] = (int32_t)sidx;
             }
             __syncthreads();
-            for (int e = threadIdx.x; e < cnt * RC * 8; e += blockDim.x) {
-                const int w = e % 8, rr = (e / 8) % RC, j = e / (8 * RC);
-                rec[j][rr][w] = (w < 7 && rr < rcn) ? src[((int64_t)(r0 + rr) * n + sid[j]) * 7 + w] : mk(0.f, 0.f);
+            for (int e = threadIdx.x; e < cnt * RC * 4; e += blockDim.x) {
+                const int rr = (e / 4) % RC, j = e / (4 * RC);
+                // chunks beyond the last right-hand side repeat it (their sums are not written)
+                stage_rec32(hdr[j], src + ((int64_t)(r0 + min(rr, rcn - 1)) * n + sid[j]) * 7, e % 4, rec[j][rr]);
             }
             __syncthreads();
             if (!active) continue;
@@ -583,16 +597,14 @@ __global__ void __launch_bounds__(TPB) k_p2p32(int nleaf, int nrhs, const int32_
                 const cx<float> g = mk(sc * cs, sc * sn);                   // e^{ikR} / (4 pi R)
                 const float iR2 = iR * iR;
                 // f = (i k R - 1) g / R^2
-                const cx<float> f = mk(iR2 * ((-ki * R - 1.f) * g.re - kr * R * g.im),
-                                       iR2 * ((-ki * R - 1.f) * g.im + kr * R * g.re));
-                const float v = q.nx * dx + q.ny * dy + q.nz * dz;
+                const float fr = LOSSY ? iR2 * (-ki * R - 1.f) : -iR2, fi = kr * iR;
+                const cx<float> f = mk(fr * g.re - fi * g.im, fr * g.im + fi * g.re);
 #pragma unroll
                 for (int rr = 0; rr < RC; ++rr) {
                     const cx<float> *qr = rec[j][rr];
-                    const cx<float> u = dx * qr[0] + dy * qr[1] + dz * qr[2];
-                    const cx<float> wx = q.nx * u - v * qr[0] - dx * qr[6];
-                    const cx<float> wy = q.ny * u - v * qr[1] - dy * qr[6];
-                    const cx<float> wz = q.nz * u - v * qr[2] - dz * qr[6];
+                    const cx<float> wx = dy * qr[2] - dz * qr[1] - dx * qr[6];
+                    const cx<float> wy = dz * qr[0] - dx * qr[2] - dy * qr[6];
+                    const cx<float> wz = dx * qr[1] - dy * qr[0] - dz * qr[6];
                     acc[rr][0] += f * wx + g * qr[3];
                     acc[rr][1] += f * wy + g * qr[4];
                     acc[rr][2] += f * wz + g * qr[5];
@@ -636,7 +648,7 @@ __global__ void __launch_bounds__(TPB) k_p2p32_pair(int nleaf, int nrhs, const i
                                                     cx<float> *__restrict__ ys0, cx<float> *__restrict__ ys1) {
     constexpr int TS = 128;
     __shared__ SrcHdr32 hdr[TS];
-    __shared__ __attribute__((aligned(16))) cx<float> rec[2][TS][8];   // a[3], b[3], n.a, unused per plan
+    __shared__ __attribute__((aligned(16))) cx<float> rec[2][TS][8];   // n x a, b, n.a, unused per plan
     __shared__ int32_t sid[TS];
     __shared__ int32_t nb_start[28], nb_box[27];
     __shared__ int n_nb;
@@ -704,10 +716,9 @@ __global__ void __launch_bounds__(TPB) k_p2p32_pair(int nleaf, int nrhs, const i
                 sid[j] = (int32_t)sidx;
             }
             __syncthreads();
-            for (int e = threadIdx.x; e < cnt * 16; e += blockDim.x) {
-                const int w = e % 8, pl = (e / 8) % 2, j = e / 16;
-                const cx<float> *sp = pl ? src1 : src0;
-                rec[pl][j][w] = w < 7 ? sp[((int64_t)r * n + sid[j]) * 7 + w] : mk(0.f, 0.f);
+            for (int e = threadIdx.x; e < cnt * 8; e += blockDim.x) {
+                const int pl = (e / 4) % 2, j = e / 8;
+                stage_rec32(hdr[j], (pl ? src1 : src0) + ((int64_t)r * n + sid[j]) * 7, e % 4, rec[pl][j]);
             }
             __syncthreads();
             if (!active) continue;
@@ -720,18 +731,17 @@ __global__ void __launch_bounds__(TPB) k_p2p32_pair(int nleaf, int nrhs, const i
                 const float iR = __builtin_amdgcn_rsqf(R2);
                 const float R = R2 * iR;
                 const float iR2 = iR * iR;
-                const float v = q.nx * dx + q.ny * dy + q.nz * dz;
                 {
                     // k0 (real): g = e^{i k0 R} / (4 pi R), f = (i k0 R - 1) g / R^2
                     const float sn = __builtin_amdgcn_sinf(krev0 * R), cs = __builtin_amdgcn_cosf(krev0 * R);
                     const float sc = self ? 0.f : inv4pi * iR;
                     const cx<float> g = mk(sc * cs, sc * sn);
-                    const cx<float> f = mk(iR2 * (-g.re - kr0 * R * g.im), iR2 * (-g.im + kr0 * R * g.re));
+                    const float fi = kr0 * iR;
+                    const cx<float> f = mk(-iR2 * g.re - fi * g.im, -iR2 * g.im + fi * g.re);
                     const cx<float> *qr = rec[0][j];
-                    const cx<float> u = dx * qr[0] + dy * qr[1] + dz * qr[2];
-                    const cx<float> wx = q.nx * u - v * qr[0] - dx * qr[6];
-                    const cx<float> wy = q.ny * u - v * qr[1] - dy * qr[6];
-                    const cx<float> wz = q.nz * u - v * qr[2] - dz * qr[6];
+                    const cx<float> wx = dy * qr[2] - dz * qr[1] - dx * qr[6];
+                    const cx<float> wy = dz * qr[0] - dx * qr[2] - dy * qr[6];
+                    const cx<float> wz = dx * qr[1] - dy * qr[0] - dz * qr[6];
                     acc0[0] += f * wx + g * qr[3];
                     acc0[1] += f * wy + g * qr[4];
                     acc0[2] += f * wz + g * qr[5];
@@ -742,13 +752,12 @@ __global__ void __launch_bounds__(TPB) k_p2p32_pair(int nleaf, int nrhs, const i
                     const float ex = __builtin_amdgcn_exp2f(kexp1 * R);
                     const float sc = self ? 0.f : inv4pi * iR * ex;
                     const cx<float> g = mk(sc * cs, sc * sn);
-                    const cx<float> f = mk(iR2 * ((-ki1 * R - 1.f) * g.re - kr1 * R * g.im),
-                                           iR2 * ((-ki1 * R - 1.f) * g.im + kr1 * R * g.re));
+                    const float fr = iR2 * (-ki1 * R - 1.f), fi = kr1 * iR;
+                    const cx<float> f = mk(fr * g.re - fi * g.im, fr * g.im + fi * g.re);
                     const cx<float> *qr = rec[1][j];
-                    const cx<float> u = dx * qr[0] + dy * qr[1] + dz * qr[2];
-                    const cx<float> wx = q.nx * u - v * qr[0] - dx * qr[6];
-                    const cx<float> wy = q.ny * u - v * qr[1] - dy * qr[6];
-                    const cx<float> wz = q.nz * u - v * qr[2] - dz * qr[6];
+                    const cx<float> wx = dy * qr[2] - dz * qr[1] - dx * qr[6];
+                    const cx<float> wy = dz * qr[0] - dx * qr[2] - dy * qr[6];
+                    const cx<float> wz = dx * qr[1] - dy * qr[0] - dz * qr[6];
                     acc1[0] += f * wx + g * qr[3];
                     acc1[1] += f * wy + g * qr[4];
                     acc1[2] += f * wz + g * qr[5];
