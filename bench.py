@@ -126,8 +126,8 @@ TRAFFIC_FILES = {
                             os.path.join(CSRC, "matvec.hip")),
     "k_p2p32": (os.path.join(ROOT, "profiles", "p2p32_torus60k_hbm_traffic.md"), os.path.join(CSRC, "matvec.hip")),
     "k_p2p32 c5": (os.path.join(ROOT, "profiles", "p2p32_ellipsoid1M_hbm_traffic.md"), os.path.join(CSRC, "matvec.hip")),
-    "k_hf_m2l_w c5": (os.path.join(ROOT, "profiles", "hf_m2l_w_ellipsoid1M_level8_hbm_traffic.md"),
-                      os.path.join(CSRC, "hf.hip")),
+    "k_rcs c5": (os.path.join(ROOT, "profiles", "rcs_ellipsoid1M_level8_hbm_traffic.md"),
+                 os.path.join(CSRC, "rcs_kernel.h")),
 }
 
 
@@ -817,14 +817,14 @@ def c5_workload(args, log):
                 "units_per_launch": p2p_pairs, "avg_launch_ms": p2p_ms, "launches_per_product": 1,
                 "traffic": measured_traffic("k_p2p32 c5"),
                 "gpairs_per_s": p2p_pairs / (p2p_ms * 1e-3) / 1e9},
-        "m2l_fine": {"kernel": "k_hf_m2l_w (finest-level S|R by rotation / coaxial shift / rotation, FP32 VALU)",
-                     "bound": "alu", "peak": PEAK["fp32_TF"], "unit": "TFLOP/s",
+        "m2l_fine": {"kernel": "k_rcs (finest-level S|R by rotation / coaxial shift / rotation, FP32 MFMA)",
+                     "bound": "mfma", "peak": PEAK["fp32_TF"], "unit": "TFLOP/s",
                      "achieved": fine_fl / (fine_ms * 1e-3) / 1e12, "per_launch_flops": fine_fl,
                      "flops_per_unit": hf_translation_flops(pl[L]), "unit_of_work": "S|R translation (3 channels)",
                      "units_per_launch": inf["m2l_pairs"][L], "order": pl[L], "avg_launch_ms": fine_ms,
-                     "launches_per_product": 1, "traffic": measured_traffic("k_hf_m2l_w c5")},
-        "m2l_all_levels": {"kernels": "k_hf_fwd / k_hf_coax / k_hf_back (orders > 20), k_hf_m2l_w (orders <= 20)",
-                           "bound": "alu", "peak": PEAK["fp32_TF"], "unit": "TFLOP/s",
+                     "launches_per_product": 1, "traffic": measured_traffic("k_rcs c5")},
+        "m2l_all_levels": {"kernels": "k_hf_fwd / k_hf_coax / k_hf_back (orders > 32), k_rcs (orders <= 32)",
+                           "bound": "mfma", "peak": PEAK["fp32_TF"], "unit": "TFLOP/s",
                            "achieved": m2l_fl / (m2l_ms * 1e-3) / 1e12, "flops_per_product": m2l_fl,
                            "ms_per_product": m2l_ms, "pairs_per_level": inf["m2l_pairs"], "order_per_level": pl},
     }
