@@ -55,7 +55,8 @@ __global__ void k_adj_gather(const cx<T> *__restrict__ y, const int32_t *__restr
 // at coefficient (n, m).  Per channel the block gathers the coefficients of L, d_x L,
 // d_y L, d_z L from the degrees below and above (one thread per (n, +-m)) as the rows
 // of leaf_eval, and each wavefront evaluates 16 nodes on the matrix cores (8 of 16
-// columns).  One evaluation per node and lane took 2.2-2.4 ms for 60k nodes at order 23 in FP64.
+// columns).  One evaluation per node and lane took 2.2-2.4 ms for 60k nodes at
+// order 23 in FP64, this 0.76-0.9 ms (both beside the other wavenumber's product).
 // out[(r n + i) 12 + e]: e = c for F_c, e = 3 + 3 i + c for d_i F_c.
 template <typename T, int TT>
 __global__ void __launch_bounds__(256) k_adj_l2p(const int32_t *__restrict__ start, const LeafNode<T> *__restrict__ geo,

@@ -90,7 +90,7 @@ __device__ inline int xcd_tile(int i, int ntiles) {
 // serial chain of a short product, a barrier and a gradient step (a branch and its LDS latency per
 // group of 4 nodes cost 3/4 of the time before GS groups were loaded together).  One thread per
 // coefficient, gathering six table entries per node, took 5.7 ms for 753k nodes at order 17
-// in FP64 and 0.81 ms for 60k at 23, now 1.74 and 0.27; 4.2 ms for 3M at 12 in FP32, now 2.2.
+// in FP64 and 0.81 ms for 60k at 23, now 1.74 and 0.27; 4.2 ms for 3M at 12 in FP32, now 1.75.
 template <typename T, int NG>
 __global__ void __launch_bounds__(384, sizeof(T) == 8 ? 2 : (NG == 16 ? 3 : 4))
     k_p2m(const int32_t *__restrict__ start, const LeafNode<T> *__restrict__ geo, const double *__restrict__ snrm,
