@@ -344,9 +344,7 @@ void l2p_t(Plan &P, int nrhs, hipStream_t s) {
     const size_t sh = (p + 1) * sizeof(T) + ((size_t)(p + 1) * (p + 3) + (size_t)(p + 1) * 16 * waves + (size_t)p * p +
                                              ((size_t)(p + 1) * (p + 2) + 2) * 4) * sizeof(cx<T>);
     auto kern = p < 8 ? k_adj_l2p<T, 4> : (p < 16 ? k_adj_l2p<T, 8> : (p < 24 ? k_adj_l2p<T, 12> : k_adj_l2p<T, 20>));
-    if (sh > 65536)
-        FMB_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                          (int)sh));
+    leaf_lds_limit(kern, sh);
     kern<<<dim3((unsigned)LL.nbox, (unsigned)nrhs), 64 * waves, sh, s>>>(
         LL.start.as<int32_t>(), P.lnode.as<LeafNode<T>>(), P.n, p, P.k_re, P.k_im,
         P.inv_alpha.as<double>() + (size_t)P.depth * p, P.btab.as<T>(), P.nrhs_max, LL.L.as<cx<T>>(), P.aws.as<cx<T>>());

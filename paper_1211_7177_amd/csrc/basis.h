@@ -78,6 +78,17 @@ __device__ __forceinline__ void leaf_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// LDS that a block of the leaf kernels may have (a CU's, less 1 KB); launches that take
+// more than the default 64 KB ask for all of it, so that plans of other orders set the same value
+constexpr size_t LEAF_LDS_MAX = 160 * 1024 - 1024;
+template <typename K>
+inline void leaf_lds_limit(K kern, size_t bytes) {
+    FMB_REQUIRE(bytes <= LEAF_LDS_MAX, "a leaf kernel's tables exceed a block's LDS");
+    if (bytes > 65536)
+        FMB_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                          (int)LEAF_LDS_MAX));
+}
+
 // What the kernels at the leaves need of a node, laid out at plan time: the direction
 // from its leaf's centre (cos th, sin th e^{i ph}), z = k r and the heads g_p, g_{p+1}
 // of the recurrence below.  The library sine, the divisions and the start above degree

@@ -317,19 +317,28 @@ __global__ void __launch_bounds__(256) k_l2p(const int32_t *__restrict__ start, 
     }
 }
 
-template <typename T, int RC>
+// LDS of k_l2p for RC right-hand sides a block
+template <typename T>
+size_t l2p_lds(int p, int rc, int waves) {
+    return (p + 1) * sizeof(T) +
+           ((size_t)(p + 1) * (p + 2) + (size_t)p * 16 * waves + (size_t)(p * (p + 1) + 2) * 3 * rc) * sizeof(cx<T>);
+}
+
+// Two right-hand sides a block share the recurrence; one at a time where two do not fit a block's LDS (FP64 leaf
+// orders from 34 with four wavefronts, 37 with one; one fits at every order: 147 KB at 40).
+template <typename T>
 void launch_l2p(Plan &P, int nrhs, const cx<T> *Lc, cx<T> *ys, hipStream_t s) {
     const int p = P.order;
     const Level &LL = P.lv[P.depth];
     // wavefronts for the nodes of an average leaf
     const int waves = (int)std::min<int64_t>(4, std::max<int64_t>(1, (P.n + 16 * LL.nbox - 1) / (16 * LL.nbox)));
-    const size_t sh = (p + 1) * sizeof(T) +
-                      ((size_t)(p + 1) * (p + 2) + (size_t)p * 16 * waves + (size_t)(p * (p + 1) + 2) * 3 * RC) * sizeof(cx<T>);
-    auto kern = p <= 8 ? k_l2p<T, RC, 4> : (p <= 16 ? k_l2p<T, RC, 8> : (p <= 24 ? k_l2p<T, RC, 12> : k_l2p<T, RC, 20>));
-    if (sh > 65536)
-        FMB_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                          (int)sh));
-    kern<<<dim3((unsigned)LL.nbox, (unsigned)((nrhs + RC - 1) / RC)), 64 * waves, sh, s>>>(
+    const int rc = nrhs > 1 && l2p_lds<T>(p, 2, waves) <= LEAF_LDS_MAX ? 2 : 1;
+    const size_t sh = l2p_lds<T>(p, rc, waves);
+    auto of = [&](auto k8, auto k16, auto k24, auto k40) { return p <= 8 ? k8 : (p <= 16 ? k16 : (p <= 24 ? k24 : k40)); };
+    auto kern = rc == 2 ? of(k_l2p<T, 2, 4>, k_l2p<T, 2, 8>, k_l2p<T, 2, 12>, k_l2p<T, 2, 20>)
+                        : of(k_l2p<T, 1, 4>, k_l2p<T, 1, 8>, k_l2p<T, 1, 12>, k_l2p<T, 1, 20>);
+    leaf_lds_limit(kern, sh);
+    kern<<<dim3((unsigned)LL.nbox, (unsigned)((nrhs + rc - 1) / rc)), 64 * waves, sh, s>>>(
         LL.start.as<int32_t>(), P.lnode.as<LeafNode<T>>(), P.n, p, P.inv_alpha.as<double>() + (size_t)P.depth * p,
         P.btab.as<T>(), nrhs, P.nrhs_max, Lc, ys);
     FMB_LAUNCH_CHECK();
@@ -1210,9 +1219,7 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
         const bool wide = P.n > 32 * LL.nbox && p2m_lds<T, 16>(p) <= 80 * 1024;
         auto kern = wide ? k_p2m<T, 16> : k_p2m<T, 8>;
         const size_t sh = wide ? p2m_lds<T, 16>(p) : p2m_lds<T, 8>(p);
-        if (sh > 65536)
-            FMB_CHECK_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
+        leaf_lds_limit(kern, sh);
         tm.begin(ST_P2M, s, ev);
         kern<<<dim3((unsigned)LL.nbox, (unsigned)nrhs), 64 * (p / 8 + 1), sh, s>>>(
             LL.start.as<int32_t>(), P.lnode.as<LeafNode<T>>(), P.snrm.as<double>(), src, n, p, P.k_re, P.k_im,
@@ -1332,8 +1339,7 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
             return true;
         }
         tm.begin(ST_L2P, s, ev);
-        if (nrhs > 1) launch_l2p<T, 2>(P, nrhs, LL.L.as<cx<T>>(), ys, s);
-        else launch_l2p<T, 1>(P, nrhs, LL.L.as<cx<T>>(), ys, s);
+        launch_l2p<T>(P, nrhs, LL.L.as<cx<T>>(), ys, s);
         tm.end(ST_L2P, s, ev);
         return true;
     }
