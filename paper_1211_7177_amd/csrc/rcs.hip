@@ -279,18 +279,22 @@ static void launch(double, int P, const RcsArgs &A, unsigned blocks, size_t lds,
     throw Status{FMB_EINVAL, "no translation kernel of this order"};
 }
 
-// Consecutive jobs of one order go out as one launch.  Sets split over zsplit blocks keep partial sums
-// for part_rhs right-hand sides: wider batches run in slices.
+// Consecutive jobs of one order go out as one launch.  A launch holds less than 2^32 threads and sets split over
+// zsplit blocks keep partial sums for part_rhs right-hand sides: wider batches run in slices.
 template <typename T>
 void rcs_run(const RcsJob *jobs, int njobs, int nrhs, int nrhs_max, hipStream_t s) {
     for (int a = 0; a < njobs;) {
         const RcsSet &F = *jobs[a].set;
         int b = a, slice = nrhs;
+        int64_t per = 0;                  // threads of one right-hand side
         for (; b < njobs && b - a < RCS_MAXLEV; ++b) {
             const RcsSet &R = *jobs[b].set;
             if (R.P != F.P) break;
             if (R.zsplit > 1) slice = std::min(slice, R.part_rhs);
+            per += (int64_t)R.ngroups * R.zsplit * (3 / R.nc) * R.waves * 64;
         }
+        FMB_REQUIRE(per < (int64_t)1 << 32, "too many translation blocks");
+        if (per) slice = (int)std::min<int64_t>(slice, (((int64_t)1 << 32) - 1) / per);
         for (int r0 = 0; r0 < nrhs; r0 += slice) {
             RcsArgs A{};
             A.nrhs_max = nrhs_max;
@@ -325,7 +329,6 @@ void rcs_run(const RcsJob *jobs, int njobs, int nrhs, int nrhs_max, hipStream_t 
                 lds = std::max(lds, R.lds);
             }
             if (blocks == 0) continue;
-            FMB_REQUIRE(blocks < ((int64_t)1 << 31), "too many translation blocks");
             launch(T(0), F.P, A, (unsigned)blocks, lds, s);
             SumArgs Z{};
             Z.nrhs = nr;
