@@ -807,14 +807,7 @@ struct Tile {
 };
 constexpr int OS_MAXCOLS = 288;                 // columns per operator-stationary job
 
-
-typedef float v4f __attribute__((ext_vector_type(4)));
-// FP32 16x16x4: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]; register q of
-// lane l holds D[4 (l / 16) + q][l % 16]
-__device__ inline v4f mma32(float a, float b, v4f c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-__device__ inline int mma32_row(int lane, int q) { return 4 * (lane >> 4) + q; }
-
-// Operator-stationary kernel for FP32 operators with 2 p^2 <= 98 (p <= 7):
+// Operator-stationary kernel for operators with 2 p^2 <= 98 (p <= 7; FP64 p <= 4):
 // a block owns one operator and a long run of that operator's columns.  Each
 // of its four waves loads the MFMA A-fragments of its RTW row tiles for the
 // whole K extent into registers once (a[i][kk] = T[16 i + l%16][4 kk + l/16]),
@@ -822,16 +815,16 @@ __device__ inline int mma32_row(int lane, int q) { return 4 * (lane >> 4) + q; }
 // Operator traffic drops from one read per 64 columns to one read per job.
 constexpr int OS_COLS = 16;
 
-template <int KS, int RTW>
+template <typename T, int KS, int RTW>
 __global__ void __launch_bounds__(TPB) k_translate_os(const Tile *__restrict__ tiles, int ntiles,
                                                       const int32_t *__restrict__ ent,
                                                       const int32_t *__restrict__ src_map,
-                                                      const float *__restrict__ ops, const float *__restrict__ X,
-                                                      float *__restrict__ Y, int KR, int ncol, int64_t blkR, int accum) {
+                                                      const T *__restrict__ ops, const T *__restrict__ X,
+                                                      T *__restrict__ Y, int KR, int ncol, int64_t blkR, int accum) {
     constexpr int KP = KS * 4;                     // K padded to whole MFMA k-steps
     constexpr int LD = (KP * OS_COLS + TPB - 1) / TPB;
-    typedef v4f v4;
-    __shared__ float Bs[2][KP][OS_COLS];
+    typedef typename Mma16<T>::v4 v4;
+    __shared__ T Bs[2][KP][OS_COLS];
     __shared__ int64_t s_in[OS_MAXCOLS], s_out[OS_MAXCOLS];
     const int tix = xcd_tile(blockIdx.x, ntiles);
     if (tix >= ntiles) return;
@@ -845,27 +838,27 @@ __global__ void __launch_bounds__(TPB) k_translate_os(const Tile *__restrict__ t
         s_out[c] = (int64_t)en * blkR + (int64_t)cc * KR;
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const float *Top = ops + (size_t)tl.op * KR * KR;
-    float a[RTW][KS];
+    const T *Top = ops + (size_t)tl.op * KR * KR;
+    T a[RTW][KS];
 #pragma unroll
     for (int i = 0; i < RTW; ++i) {
         const int row = (wave * RTW + i) * 16 + (lane & 15);
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
             const int k = 4 * kk + (lane >> 4);
-            a[i][kk] = (row < KR && k < KR) ? Top[(size_t)row * KR + k] : 0.f;
+            a[i][kk] = (row < KR && k < KR) ? Top[(size_t)row * KR + k] : T(0);
         }
     }
     __syncthreads();
     const int ntc = (C + OS_COLS - 1) / OS_COLS;
-    float pre[LD];
+    T pre[LD];
     auto fetch = [&](int t) {
 #pragma unroll
         for (int j = 0; j < LD; ++j) {
             const int e = threadIdx.x + j * TPB;
             const int c = e / KP, k = e % KP;
             const int cg = t * OS_COLS + c;
-            pre[j] = (e < KP * OS_COLS && cg < C && k < KR) ? X[s_in[cg] + k] : 0.f;
+            pre[j] = (e < KP * OS_COLS && cg < C && k < KR) ? X[s_in[cg] + k] : T(0);
         }
     };
     auto stash = [&](int buf) {
@@ -886,18 +879,18 @@ __global__ void __launch_bounds__(TPB) k_translate_os(const Tile *__restrict__ t
         for (int i = 0; i < RTW; ++i) acc[i] = v4{0, 0, 0, 0};
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
-            const float b = Bs[buf][4 * kk + (lane >> 4)][lane & 15];
+            const T b = Bs[buf][4 * kk + (lane >> 4)][lane & 15];
 #pragma unroll
-            for (int i = 0; i < RTW; ++i) acc[i] = mma32(a[i][kk], b, acc[i]);
+            for (int i = 0; i < RTW; ++i) acc[i] = Mma16<T>::mma(a[i][kk], b, acc[i]);
         }
         const int cg = t * OS_COLS + (lane & 15);
         if (cg < C) {
-            float *yo = Y + s_out[cg];
+            T *yo = Y + s_out[cg];
 #pragma unroll
             for (int i = 0; i < RTW; ++i)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int row = (wave * RTW + i) * 16 + mma32_row(lane, q);
+                    const int row = (wave * RTW + i) * 16 + Mma16<T>::row(lane >> 4, q);
                     if (row < KR) yo[row] = accum ? yo[row] + acc[i][q] : acc[i][q];
                 }
         }
@@ -909,7 +902,10 @@ __global__ void __launch_bounds__(TPB) k_translate_os(const Tile *__restrict__ t
 // columns per split-BF16 job (the instantiations in launch_translate)
 inline int bf3_job_cols(int p) { return p <= 5 ? 96 : (p <= 8 ? 64 : 32); }
 
-inline bool use_bf3(const Plan &P) { return P.translate_mode == FMB_TRANSLATE_BF16X3; }
+// (of dense plans)
+inline bool use_bf3(const Plan &P) {
+    return P.precision == FMB_FP32 && P.translate_mode == FMB_TRANSLATE_BF16X3 && P.order >= 2;
+}
 
 // right-hand sides per translation launch: a job holds whole entries of 3 x (this many)
 // columns, so wider batches run as several launches over slices of the right-hand sides
@@ -940,7 +936,7 @@ __global__ void __launch_bounds__(TPB) k_translate_bf3(const Tile *__restrict__ 
     constexpr int KP = KS * 32;
     constexpr int CS = KP + 4;                                   // LDS column stride (floats)
     constexpr int LD = (KP * JC + TPB - 1) / TPB;
-    typedef v4f v4;
+    typedef Mma16<float>::v4 v4;
     constexpr int RP = 64 * RTW + 1;                             // output tile pitch (rows of 4 waves)
     __shared__ __attribute__((aligned(16))) float Bs[JC][CS];
     __shared__ float Os[16][RP];
@@ -1075,39 +1071,51 @@ void launch_bf3(int p, unsigned g, const Tile *tiles, int64_t ntiles, const int3
 
 // role: 0 S|S, 1 S|R, 2 R|R (names the split-BF16 launches in kernel traces);
 // accum: add the products into Y instead of overwriting it
-void launch_translate(const Tile *tiles, int64_t ntiles, const int32_t *ent, const int32_t *src_map, const float *ops,
-                      const float *x, float *y, int KR, int ncol, int64_t blkR, hipStream_t s, int role, int accum,
+template <typename T>
+void launch_translate(const Tile *tiles, int64_t ntiles, const int32_t *ent, const int32_t *src_map, const T *ops,
+                      const T *x, T *y, int KR, int ncol, int64_t blkR, hipStream_t s, int role, int accum,
                       const void *fhi, const void *flo) {
     if (ntiles <= 0) return;
-    if (fhi) {
-        // split-BF16 translations (FP32 plans only, checked by use_bf3)
-        const int p = (int)lround(sqrt(KR / 2.0));
-        const int RT = (KR + 15) / 16;
-        // register tiles per instantiation below: KS k-steps of 32, 4 waves x RTW row tiles of 16
-        static const int ks_of[10] = {0, 0, 1, 1, 1, 2, 3, 4, 4, 6}, rtw_of[10] = {0, 0, 1, 1, 1, 1, 2, 2, 2, 3};
-        if (p < 2 || p > 9 || 2 * p * p != KR || (KR + 31) / 32 != ks_of[p] || RT > 4 * rtw_of[p])
-            throw std::runtime_error("split-BF16 translation: unsupported operator size");
-        const unsigned g = (unsigned)(((ntiles + 7) / 8) * 8);
-        const bf16x8 *h = (const bf16x8 *)fhi, *l = (const bf16x8 *)flo;
-        switch (role) {
-        case 0: launch_bf3<0>(p, g, tiles, ntiles, ent, src_map, h, l, x, y, KR, RT, ncol, blkR, accum, s); break;
-        case 1: launch_bf3<1>(p, g, tiles, ntiles, ent, src_map, h, l, x, y, KR, RT, ncol, blkR, accum, s); break;
-            default: launch_bf3<2>(p, g, tiles, ntiles, ent, src_map, h, l, x, y, KR, RT, ncol, blkR, accum, s); break;
-        }
-        FMB_LAUNCH_CHECK();
-        return;
-    }
-    const unsigned g = (unsigned)(((ntiles + 7) / 8) * 8);
-    const float *o = ops;
     const int p = (int)lround(sqrt(KR / 2.0));
-    switch (p) {
-        case 2: k_translate_os<2, 1><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
-        case 3: k_translate_os<5, 1><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
-        case 4: k_translate_os<8, 1><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
-        case 5: k_translate_os<13, 1><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
-        case 6: k_translate_os<18, 2><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
-        case 7: k_translate_os<25, 2><<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, o, x, y, KR, ncol, blkR, accum); break;
-        default: throw std::runtime_error("FP32 translation: unsupported operator size");
+    const unsigned g = (unsigned)(((ntiles + 7) / 8) * 8);
+    if constexpr (sizeof(T) == sizeof(float)) {
+        if (fhi) {
+            // split-BF16 translations (checked by use_bf3)
+            const int RT = (KR + 15) / 16;
+            // register tiles per instantiation below: KS k-steps of 32, 4 waves x RTW row tiles of 16
+            static const int ks_of[10] = {0, 0, 1, 1, 1, 2, 3, 4, 4, 6}, rtw_of[10] = {0, 0, 1, 1, 1, 1, 2, 2, 2, 3};
+            if (p < 2 || p > 9 || 2 * p * p != KR || (KR + 31) / 32 != ks_of[p] || RT > 4 * rtw_of[p])
+                throw std::runtime_error("split-BF16 translation: unsupported operator size");
+            const bf16x8 *h = (const bf16x8 *)fhi, *l = (const bf16x8 *)flo;
+            switch (role) {
+                case 0: launch_bf3<0>(p, g, tiles, ntiles, ent, src_map, h, l, x, y, KR, RT, ncol, blkR, accum, s); break;
+                case 1: launch_bf3<1>(p, g, tiles, ntiles, ent, src_map, h, l, x, y, KR, RT, ncol, blkR, accum, s); break;
+                default: launch_bf3<2>(p, g, tiles, ntiles, ent, src_map, h, l, x, y, KR, RT, ncol, blkR, accum, s); break;
+            }
+            FMB_LAUNCH_CHECK();
+            return;
+        }
+    }
+    auto go = [&](auto kern) { kern<<<g, TPB, 0, s>>>(tiles, (int)ntiles, ent, src_map, ops, x, y, KR, ncol, blkR, accum); };
+    if constexpr (sizeof(T) == sizeof(float)) {
+        switch (p) {
+            case 1: go(k_translate_os<T, 1, 1>); break;
+            case 2: go(k_translate_os<T, 2, 1>); break;
+            case 3: go(k_translate_os<T, 5, 1>); break;
+            case 4: go(k_translate_os<T, 8, 1>); break;
+            case 5: go(k_translate_os<T, 13, 1>); break;
+            case 6: go(k_translate_os<T, 18, 2>); break;
+            case 7: go(k_translate_os<T, 25, 2>); break;
+            default: throw std::runtime_error("FP32 translation: unsupported operator size");
+        }
+    } else {
+        switch (p) {
+            case 1: go(k_translate_os<T, 1, 1>); break;
+            case 2: go(k_translate_os<T, 2, 1>); break;
+            case 3: go(k_translate_os<T, 5, 1>); break;
+            case 4: go(k_translate_os<T, 8, 1>); break;
+            default: throw std::runtime_error("FP64 translation: unsupported operator size");
+        }
     }
     FMB_LAUNCH_CHECK();
 }
@@ -1115,14 +1123,15 @@ void launch_translate(const Tile *tiles, int64_t ntiles, const int32_t *ent, con
 // parent (level l) multipole = sum of its children's translated slots
 // Column sums of a row range [e0, e1) of slots (rows of blk complex values, the
 // first ncolP2 of which are used) by one block: columns go in chunks of
-// CW = min(ncolP2, 128); within a chunk G = TPB / CW row groups take rows
+// CW = min(ncolP2, 128) (FP64: 32, so that a column's sum does not depend on the
+// number of right-hand sides); within a chunk G = TPB / CW row groups take rows
 // e0 + g, e0 + g + G, ... and their partial sums are added in group order, so
 // the result does not depend on timing.
 template <typename T>
 __device__ inline void slot_sum(const cx<T> *__restrict__ Y, int e0, int e1, int64_t blk, int ncolP2,
                                 cx<T> *__restrict__ out, bool accumulate, cx<T> *sm) {
     const int t = threadIdx.x;
-    const int CW = min(ncolP2, 128), G = TPB / CW;
+    const int CW = sizeof(T) == 8 ? 32 : min(ncolP2, 128), G = TPB / CW;
     const int g = t / CW, c = t % CW;
     for (int c0 = 0; c0 < ncolP2; c0 += CW) {
         const int cw = min(CW, ncolP2 - c0);
@@ -1242,9 +1251,9 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
         if (V.ntiles_m2m == 0) return true;
         tm.begin(ST_M2M, s, ev);
         for (int r0 = 0; r0 < nrhs; r0 += cw)
-            launch_translate(V.tiles_m2m.as<Tile>(), V.ntiles_m2m, C.by_octant.as<int32_t>(), nullptr, V.m2m.as<float>(),
-                             (const float *)C.M.p + roff(r0), (float *)yb + roff(r0), KR, 3 * std::min(cw, nrhs - r0),
-                             blkR, s, 0, 0, bf3 ? V.m2m_hi.p : nullptr, V.m2m_lo.p);
+            launch_translate<T>(V.tiles_m2m.as<Tile>(), V.ntiles_m2m, C.by_octant.as<int32_t>(), nullptr, V.m2m.as<T>(),
+                                (const T *)C.M.p + roff(r0), (T *)yb + roff(r0), KR, 3 * std::min(cw, nrhs - r0),
+                                blkR, s, 0, 0, bf3 ? V.m2m_hi.p : nullptr, V.m2m_lo.p);
         tm.end(ST_M2M, s, ev, (nrhs + cw - 1) / cw);
         tm.begin(ST_SUMS, s, ev);
         k_sum_children<T><<<(unsigned)V.nbox, TPB, 0, s>>>(V.child_start.as<int32_t>(), V.nbox, yb, V.M.as<cx<T>>(), blk,
@@ -1277,10 +1286,10 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
             Level &V = P.lv[l];
             if (V.ntiles_m2l == 0) continue;
             for (int r0 = 0; r0 < nrhs; r0 += cw) {
-                launch_translate(V.tiles_m2l.as<Tile>(), V.ntiles_m2l, V.ff_by_op.as<int32_t>(),
-                                    V.ff_src.as<int32_t>(), V.m2l.as<float>(), (const float *)V.M.p + roff(r0),
-                                 (float *)(yb + V.slot_base * blk) + roff(r0), KR, 3 * std::min(cw, nrhs - r0), blkR,
-                                 s, 1, 0, bf3 ? V.m2l_hi.p : nullptr, V.m2l_lo.p);
+                launch_translate<T>(V.tiles_m2l.as<Tile>(), V.ntiles_m2l, V.ff_by_op.as<int32_t>(),
+                                    V.ff_src.as<int32_t>(), V.m2l.as<T>(), (const T *)V.M.p + roff(r0),
+                                    (T *)(yb + V.slot_base * blk) + roff(r0), KR, 3 * std::min(cw, nrhs - r0), blkR,
+                                    s, 1, 0, bf3 ? V.m2l_hi.p : nullptr, V.m2l_lo.p);
                 ++nk;
             }
         }
@@ -1323,10 +1332,9 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
         Level &U = P.lv[l - 1];
         tm.begin(ST_L2L, s, ev);
         for (int r0 = 0; r0 < nrhs; r0 += cw)
-            launch_translate(V.tiles_l2l.as<Tile>(), V.ntiles_l2l, V.by_octant.as<int32_t>(), V.parent.as<int32_t>(),
-                                V.l2l.as<float>(), (const float *)U.L.p + roff(r0), (float *)V.L.p + roff(r0), KR,
-                             3 * std::min(cw, nrhs - r0), blkR, s, 2, 1, bf3 ? V.l2l_hi.p : nullptr,
-                                V.l2l_lo.p);
+            launch_translate<T>(V.tiles_l2l.as<Tile>(), V.ntiles_l2l, V.by_octant.as<int32_t>(), V.parent.as<int32_t>(),
+                                V.l2l.as<T>(), (const T *)U.L.p + roff(r0), (T *)V.L.p + roff(r0), KR,
+                                3 * std::min(cw, nrhs - r0), blkR, s, 2, 1, bf3 ? V.l2l_hi.p : nullptr, V.l2l_lo.p);
         tm.end(ST_L2L, s, ev, (nrhs + cw - 1) / cw);
         return true;
     }
@@ -1398,12 +1406,16 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
 // target job count per launch: about 12 resident blocks on each of the 256 CUs
 constexpr int64_t EP_BLOCKS = 3072;
 
-// Dense operators serve FP32 plans of one order up to 9 with split-BF16 products and up to 7 in FP32: there one small
-// GEMM per offset costs less than walking a class's tiles through LDS.  One product, dense against rotation / shift
+// Dense operators serve plans of one small order: there one small GEMM per offset costs less than walking a class's
+// tiles through LDS.  FP32 up to order 7, 9 with split-BF16 products.  One product, dense against rotation / shift
 // (ms; torus 60,000 nodes, sphere 3,840): FP32 p = 7 0.60 / 0.57, 0.212 / 0.227; p = 8 0.81 / 0.69, 0.29 / 0.24;
-// split-BF16 p = 9 0.76 / 0.81, 0.235 / 0.263.
+// split-BF16 p = 9 0.76 / 0.81, 0.235 / 0.263; FP32 p = 1 0.172 / 0.241, 0.054 / 0.077.  FP64 up to order 4 (p = 1
+// 0.264 / 0.386, 0.059 / 0.100; p = 4 0.363 / 0.459, 0.085 / 0.115): above it the slots, which hold the result of every
+// pair, outgrow what they save (GEMMs of the larger FP64 operators p = 5 0.76 / 0.49, 0.161 / 0.124; p = 9 1.85 / 0.81,
+// 0.347 / 0.192 and 846 / 103 MB).
 bool dense_order(int precision, int translate_mode, int p) {
-    return precision == FMB_FP32 && p >= 2 && p <= (translate_mode == FMB_TRANSLATE_BF16X3 ? 9 : 7);
+    if (precision == FMB_FP64) return p <= 4;
+    return p <= (translate_mode == FMB_TRANSLATE_BF16X3 ? 9 : 7);
 }
 
 void build_tiles(Plan &P, hipStream_t s) {

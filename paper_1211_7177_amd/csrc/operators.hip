@@ -1,5 +1,5 @@
 // Dense translation operators of the upward and downward passes (eqs. 2.20-2.21)
-// for FP32 plans of one small order, built in FP64 on the GPU.
+// for plans of one small order, built in FP64 on the GPU.
 //
 // Expansions use R_n^m = j_n(k r) Y_n^m and S_n^m = h_n(k r) Y_n^m (eq. 2.16)
 // with Y of eq. 2.15.  From the plane-wave form of the regular solutions,
@@ -347,7 +347,7 @@ void build_operators(Plan &P, hipStream_t s) {
     const int p = P.order, P2 = p * p, L = P.depth;
     const int Lm = 2 * p - 2;
     const int Q = 2 * p + 2;
-    const size_t esz = sizeof(float);
+    const size_t esz = P.precision == FMB_FP64 ? sizeof(double) : sizeof(float);
     DevBuf gx, gw, tab, gaunt;
     gx.alloc(Q * sizeof(double));
     gw.alloc(Q * sizeof(double));
@@ -379,8 +379,12 @@ void build_operators(Plan &P, hipStream_t s) {
         DevBuf dd;
         dd.alloc(ds.size() * sizeof(OpDesc));
         FMB_CHECK_HIP(hipMemcpyAsync(dd.p, ds.data(), ds.size() * sizeof(OpDesc), hipMemcpyHostToDevice, s));
-        k_build_op<float><<<(unsigned)ds.size(), TPB, shmem, s>>>(dd.as<OpDesc>(), p, P.k_re, P.k_im, gaunt.as<double>(),
-                                                                    alpha.as<double>(), outbuf.as<float>());
+        auto build = [&](auto kern, auto *out) {
+            kern<<<(unsigned)ds.size(), TPB, shmem, s>>>(dd.as<OpDesc>(), p, P.k_re, P.k_im, gaunt.as<double>(),
+                                                         alpha.as<double>(), out);
+        };
+        if (P.precision == FMB_FP64) build(k_build_op<double>, outbuf.as<double>());
+        else build(k_build_op<float>, outbuf.as<float>());
         FMB_LAUNCH_CHECK();
         FMB_CHECK_HIP(hipStreamSynchronize(s));
     };

@@ -1,0 +1,65 @@
+"""Plans of the lowest orders translate by dense operators: double precision up to
+order 4, single precision from order 1."""
+
+import numpy as np
+import pytest
+
+from synthetic import complex_normal, meshes, nystrom3
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def body():
+    q = nystrom3(meshes.geodesic_ellipsoid((1.5, 1.0, 0.75), 5))
+    n = q["points"].shape[0]
+    return q, complex_normal((100, n, 3), 61), complex_normal((100, n, 3), 62)
+
+
+def _plan(q, order, precision, k=1.5 + 0.25j, **kw):
+    from paper_1211_7177_amd import Plan
+    return Plan(q["points"], q["normals"], q["weights"], k, order, depth=4, precision=precision, corr="none",
+                point_tri=q["point_tri"], **kw)
+
+
+@pytest.mark.parametrize("precision,order,translate", [("fp64", 1, "fp32"), ("fp64", 2, "fp32"), ("fp64", 3, "fp32"),
+                                                       ("fp64", 4, "fp32"),
+                                                       ("fp32", 1, "fp32"), ("fp32", 1, "bf16x3")])
+def test_lowest_orders_run_dense_operators(body, precision, order, translate):
+    """The sums over slots, which only dense plans have, are timed; 100 right-hand sides (a job holds 96) equal
+    single calls, bit for bit in double precision and to 1e-5 in single; <A(a, b), y> = <(a, b), A^H y> holds to
+    rounding (1e-12 and 1e-4 of the norms): the adjoint is the transpose of the truncated product."""
+    q, a, b = body
+    print("low order", precision, order, translate, flush=True)
+    P = _plan(q, order, precision, nrhs_max=100, translate=translate)
+    dt = torch.complex128 if precision == "fp64" else torch.complex64
+    ga, gb = (torch.as_tensor(u, device="cuda").to(dt) for u in (a, b))
+    P.profile(True)
+    y = P.matvec(ga, gb)
+    assert P.profile_read()["sums"][1] > 0
+    P.profile(False)
+    for r in (0, 95, 96, 99):
+        one = P.matvec(ga[r], gb[r])
+        assert torch.equal(one, y[r]) if precision == "fp64" else torch.linalg.norm(one - y[r]) <= 1e-5 * torch.linalg.norm(one)
+    v = complex_normal(a.shape[1:], 63)
+    va, vb = (u.cpu().numpy().astype(complex) for u in P.matvec_adjoint(torch.as_tensor(v, device="cuda").to(dt)))
+    out = y[0].cpu().numpy().astype(complex)
+    gap = abs(np.vdot(v, out) - np.vdot(va, a[0]) - np.vdot(vb, b[0]))
+    assert gap <= (1e-4 if precision == "fp32" else 1e-12) * np.linalg.norm(v) * np.linalg.norm(out)
+    P.close()
+
+
+@pytest.mark.parametrize("order", [3, 4])
+def test_dense_and_rotated_translations_agree(body, order):
+    """A plan asked for 10^-(p - 0.5)/2.8 has order p at every level and translates by rotation and axial shift: the
+    same truncated sums, so the two differ by rounding alone (1e-13 after sums over 3 levels)."""
+    q, a, b = body
+    k = 0.5 + 0.1j                  # boxes of 0.75 at the top: larger k asks for more than order 3 there
+    D, R = _plan(q, order, "fp64", k), _plan(q, 0, "fp64", k, tol=10.0 ** (-(order - 0.5) / 2.8))
+    assert R.info()["order_level"][2:] == [order] * 3
+    ga, gb = (torch.as_tensor(u[0], device="cuda") for u in (a, b))
+    d, r = D.matvec(ga, gb), R.matvec(ga, gb)
+    assert torch.linalg.norm(d - r) <= 1e-13 * torch.linalg.norm(d)
+    D.close()
+    R.close()
