@@ -253,6 +253,20 @@ size_t p2m_lds(int N) {
            std::max((size_t)(N + 1) * 4 * NG, (size_t)28 * (2 * N + 1)) * sizeof(cx<T>);
 }
 
+// Chunks of 64 nodes instead of 32, where two blocks' tables fit a CU: when a leaf has more than 32 on average, or when
+// some leaf has and the grid is short, so that the fullest leaves' second chunk would be waited for.  Short: two rounds
+// of what the CUs hold by LDS (eight blocks at most), for the plan's largest batch, so that a column's sums do not depend
+// on how many there are.  Chunks of 32 / 64, fullest leaf 40 or 59 (us): 532 leaves FP32 p = 5 31 / 21, FP64 p = 16
+// 66 / 58; 2,320 leaves FP32 p = 5 36 / 27, FP64 p = 16 156 / 178; 4,256 blocks FP64 p = 16 207 / 280.
+template <typename T>
+bool p2m_wide(const Plan &P) {
+    const size_t lds = p2m_lds<T, 16>(P.order);
+    const int64_t nbox = P.lv[P.depth].nbox;
+    if (lds > 80 * 1024) return false;
+    return P.n > 32 * nbox ||
+           (P.leaf_max > 32 && nbox * P.nrhs_max <= 512 * (int64_t)std::min<size_t>(8, LEAF_LDS_MAX / lds));
+}
+
 // ---------------------------------------------------------------- L2P
 // One block per leaf and RC right-hand sides, 16 nodes per wavefront at a time: the
 // coefficients are laid out once per block as the rows that leaf_eval multiplies
@@ -1224,8 +1238,7 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
     if (step == k++) {
         if (!far) return true;
         FMB_REQUIRE(p <= 40, "leaf order too large for the multipole kernel");
-        // chunks of 64 nodes when a leaf has more than 32 on average and two blocks' tables fit a CU
-        const bool wide = P.n > 32 * LL.nbox && p2m_lds<T, 16>(p) <= 80 * 1024;
+        const bool wide = p2m_wide<T>(P);
         auto kern = wide ? k_p2m<T, 16> : k_p2m<T, 8>;
         const size_t sh = wide ? p2m_lds<T, 16>(p) : p2m_lds<T, 8>(p);
         leaf_lds_limit(kern, sh);

@@ -90,7 +90,7 @@ struct Plan {
     double k_re = 0, k_im = 0;
     double lo[3] = {0, 0, 0}, ext = 0;
     int64_t ntri = 0, tri_m = 1;
-    int64_t p2p_pairs = 0;
+    int64_t p2p_pairs = 0, leaf_max = 0;   // near pairs, nodes of the fullest leaf
     int leaf_target = 32;
     int translate_mode = FMB_TRANSLATE_FP32;
     // lossy wavenumbers: levels below far_lmin keep no far field (depth + 1: local only); a

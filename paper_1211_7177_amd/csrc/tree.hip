@@ -360,6 +360,7 @@ __global__ void k_gather_nodes(const double *__restrict__ pts, const double *__r
     stri[i] = tri[u];
 }
 
+// near pairs, and the nodes of the fullest leaf
 __global__ void k_p2p_pairs(const int32_t *__restrict__ start, const int32_t *__restrict__ nbr, int64_t nbox,
                             unsigned long long *__restrict__ total) {
     int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -370,6 +371,7 @@ __global__ void k_p2p_pairs(const int32_t *__restrict__ start, const int32_t *__
         if (q >= 0) ns += start[q + 1] - start[q];
     }
     atomicAdd(total, (unsigned long long)(ns * (start[b + 1] - start[b])));
+    atomicMax(total + 1, (unsigned long long)(start[b + 1] - start[b]));
 }
 
 __global__ void k_incl_to_excl(int32_t *__restrict__ d, const int32_t *__restrict__ incl, int64_t m) {
@@ -614,15 +616,16 @@ void build_tree(Plan &P, const double *d_pts, hipStream_t s, const int32_t *host
     // near-pair count (statistics)
     {
         DevBuf tot;
-        tot.alloc(sizeof(unsigned long long));
-        FMB_CHECK_HIP(hipMemsetAsync(tot.p, 0, sizeof(unsigned long long), s));
+        unsigned long long h[2] = {0, 0};
+        tot.alloc(sizeof(h));
+        FMB_CHECK_HIP(hipMemsetAsync(tot.p, 0, sizeof(h), s));
         k_p2p_pairs<<<grid_for(P.lv[L].nbox), TPB, 0, s>>>(P.lv[L].start.as<int32_t>(), P.lv[L].nbr.as<int32_t>(),
                                                             P.lv[L].nbox, tot.as<unsigned long long>());
         FMB_LAUNCH_CHECK();
-        unsigned long long h = 0;
-        FMB_CHECK_HIP(hipMemcpyAsync(&h, tot.p, sizeof(h), hipMemcpyDeviceToHost, s));
+        FMB_CHECK_HIP(hipMemcpyAsync(h, tot.p, sizeof(h), hipMemcpyDeviceToHost, s));
         FMB_CHECK_HIP(hipStreamSynchronize(s));
-        P.p2p_pairs = (int64_t)h;
+        P.p2p_pairs = (int64_t)h[0];
+        P.leaf_max = (int64_t)h[1];
     }
 }
 
