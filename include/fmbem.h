@@ -190,10 +190,12 @@ int fmm_plan_destroy(fmb_plan_t plan);
  * M2M (S|S translation kernel), M2L (S|R translation kernel), L2L (R|R), L2P,
  * P2P, corrections (with the return to user order, plans with corrections),
  * scatter (the return to user order, plans without corrections), sums (the
- * per-target sums of the S|S and S|R translation slots), and the finest level's
- * S|R launch alone (plans with an order per level; its launch is also counted
- * in M2L).  ms and launches: host arrays of FMB_NSTAGES entries (either may be
- * NULL).
+ * per-target sums of the S|S and S|R translation slots of dense plans), and the
+ * finest level's S|R launches alone (plans that translate by rotation; they are
+ * also counted in M2L).  Levels of one order share an S|R launch, and the
+ * partial sums of split ones a second; with the last stage timed the finest
+ * level runs in launches of its own.  ms and launches: host arrays of
+ * FMB_NSTAGES entries (either may be NULL).
  */
 #define FMB_NSTAGES 11
 #define FMB_PROFILE_ALL 0x7ff

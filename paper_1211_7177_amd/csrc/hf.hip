@@ -742,13 +742,13 @@ void build_hf(Plan &P, hipStream_t s) {
 
 // three-launch translation set: npairs pairs (source box src_idx[e] or e, direction dir[e] + dir_add)
 // into ndst destinations (pairs of b: dst_ofs[b] .. dst_ofs[b+1], or e = b); mck / nmck / mck_max: the
-// |m| chunks of this coaxial shift
+// |m| chunks of this coaxial shift; returns the kernels it launched
 template <typename T>
-void hf_pipe(Plan &P, int nrhs, hipStream_t s, int64_t npairs, const int32_t *src_idx, const int32_t *dir,
+int hf_pipe(Plan &P, int nrhs, hipStream_t s, int64_t npairs, const int32_t *src_idx, const int32_t *dir,
              int dir_add, const int32_t *dinfo, const T *W, int64_t wsz, const cx<T> *ph, int phs, const cx<T> *C,
              int64_t csz, const Level &Vs, const Level &Vd, const DevBuf &mck, int nmck, int mck_max, int64_t ndst,
              const int32_t *dst_ofs, int accumulate, const cx<T> *S, cx<T> *D) {
-    if (npairs == 0 || ndst == 0) return;
+    if (npairs == 0 || ndst == 0) return 0;
     const int ps = Vs.p, pd = Vd.p;
     if (Vs.hnck_max > HF_CHUNK_MAX || Vd.hnck_max > HF_CHUNK_MAX || mck_max > HF_CHUNK_MAX)
         throw Status{FMB_EINVAL, "translation chunk larger than the kernels hold"};
@@ -759,6 +759,7 @@ void hf_pipe(Plan &P, int nrhs, hipStream_t s, int64_t npairs, const int32_t *sr
     if ((size_t)rc * per > std::min(P.hX1.bytes, P.hX2.bytes))
         throw Status{FMB_EINVAL, "pipeline scratch smaller than one right-hand side"};
     const int64_t S2 = (int64_t)ps * ps, D2 = (int64_t)pd * pd;
+    int nk = 0;
     for (int r0 = 0; r0 < nrhs; r0 += rc) {
         const int nr = std::min(rc, nrhs - r0);
         // right-hand side r0 of every box starts r0 * 3 p^2 into the box's block
@@ -777,26 +778,28 @@ void hf_pipe(Plan &P, int nrhs, hipStream_t s, int64_t npairs, const int32_t *sr
                                                                      Vd.hnck.as<int32_t>(), pd, P.nrhs_max, nr,
                                                                      accumulate, X2, Dr);
         FMB_LAUNCH_CHECK();
+        nk += 3;
     }
+    return nk;
 }
 
 template <typename T>
-void hf_m2m(Plan &P, int l, int nrhs, hipStream_t s) {
+int hf_m2m(Plan &P, int l, int nrhs, hipStream_t s) {
     Level &V = P.lv[l], &Cv = P.lv[l + 1];
     if (V.r_m2m.on) {
         const RcsJob job{&V.r_m2m, Cv.M.p, V.M.p, 0};
-        rcs_run<T>(&job, 1, nrhs, P.nrhs_max, s);
-        return;
+        return rcs_run<T>(&job, 1, nrhs, P.nrhs_max, s);
     }
-    hf_pipe<T>(P, nrhs, s, Cv.nbox, nullptr, Cv.octant.as<int32_t>(), 0, V.hoinfo.as<int32_t>(), V.hWo.as<T>(),
+    return hf_pipe<T>(P, nrhs, s, Cv.nbox, nullptr, Cv.octant.as<int32_t>(), 0, V.hoinfo.as<int32_t>(), V.hWo.as<T>(),
                V.hwszo, V.hpho.as<cx<T>>(), V.hpwo, V.hCss.as<cx<T>>(), 0, Cv, V, V.hmck_ss, V.hnmck_ss,
                V.hmck_ss_max, V.nbox, V.child_start.as<int32_t>(), 0, Cv.M.as<cx<T>>(), V.M.as<cx<T>>());
 }
 
 // S|R into levels l0 .. l1: the pipelined levels one by one, the others in as few launches as their shapes allow
 template <typename T>
-void hf_m2l(Plan &P, int l0, int l1, int nrhs, hipStream_t s) {
+int hf_m2l(Plan &P, int l0, int l1, int nrhs, hipStream_t s) {
     std::vector<RcsJob> jobs;
+    int nk = 0;
     for (int l = l0; l <= l1; ++l) {
         Level &V = P.lv[l];
         if (V.nff == 0) {
@@ -804,35 +807,35 @@ void hf_m2l(Plan &P, int l0, int l1, int nrhs, hipStream_t s) {
             const int64_t m = V.nbox * P.nrhs_max * 3 * (int64_t)V.p * V.p;
             k_hf_zero<T><<<(unsigned)((m + HTPB - 1) / HTPB), HTPB, 0, s>>>(V.L.as<cx<T>>(), m);
             FMB_LAUNCH_CHECK();
+            ++nk;
         } else if (V.r_m2l.on) {
             jobs.push_back(RcsJob{&V.r_m2l, V.M.p, V.L.p, 0});
         } else {
-            hf_pipe<T>(P, nrhs, s, V.nff, V.ff_src.as<int32_t>(), V.ff_op.as<int32_t>(), 0, V.hopi.as<int32_t>(),
+            nk += hf_pipe<T>(P, nrhs, s, V.nff, V.ff_src.as<int32_t>(), V.ff_op.as<int32_t>(), 0, V.hopi.as<int32_t>(),
                        V.hW.as<T>(), V.hwsz, V.hph.as<cx<T>>(), V.p, V.hC.as<cx<T>>(), V.hcsz, V, V, V.hmck, V.hnmck,
                        V.hmck_max, V.nbox, V.ff_ofs.as<int32_t>(), 0, V.M.as<cx<T>>(), V.L.as<cx<T>>());
         }
     }
-    rcs_run<T>(jobs.data(), (int)jobs.size(), nrhs, P.nrhs_max, s);
+    return nk + rcs_run<T>(jobs.data(), (int)jobs.size(), nrhs, P.nrhs_max, s);
 }
 
 template <typename T>
-void hf_l2l(Plan &P, int l, int nrhs, hipStream_t s) {
+int hf_l2l(Plan &P, int l, int nrhs, hipStream_t s) {
     Level &V = P.lv[l], &U = P.lv[l - 1];
     if (V.r_l2l.on) {
         const RcsJob job{&V.r_l2l, U.L.p, V.L.p, 1};
-        rcs_run<T>(&job, 1, nrhs, P.nrhs_max, s);
-        return;
+        return rcs_run<T>(&job, 1, nrhs, P.nrhs_max, s);
     }
-    hf_pipe<T>(P, nrhs, s, V.nbox, V.parent.as<int32_t>(), V.octant.as<int32_t>(), 8, V.hoinfo.as<int32_t>(),
+    return hf_pipe<T>(P, nrhs, s, V.nbox, V.parent.as<int32_t>(), V.octant.as<int32_t>(), 8, V.hoinfo.as<int32_t>(),
                V.hWo.as<T>(), V.hwszo, V.hpho.as<cx<T>>(), V.hpwo, V.hCrr.as<cx<T>>(), 0, U, V, V.hmck_rr,
                V.hnmck_rr, V.hmck_rr_max, V.nbox, nullptr, 1, U.L.as<cx<T>>(), V.L.as<cx<T>>());
 }
 
-template void hf_m2m<float>(Plan &, int, int, hipStream_t);
-template void hf_m2m<double>(Plan &, int, int, hipStream_t);
-template void hf_m2l<float>(Plan &, int, int, int, hipStream_t);
-template void hf_m2l<double>(Plan &, int, int, int, hipStream_t);
-template void hf_l2l<float>(Plan &, int, int, hipStream_t);
-template void hf_l2l<double>(Plan &, int, int, hipStream_t);
+template int hf_m2m<float>(Plan &, int, int, hipStream_t);
+template int hf_m2m<double>(Plan &, int, int, hipStream_t);
+template int hf_m2l<float>(Plan &, int, int, int, hipStream_t);
+template int hf_m2l<double>(Plan &, int, int, int, hipStream_t);
+template int hf_l2l<float>(Plan &, int, int, hipStream_t);
+template int hf_l2l<double>(Plan &, int, int, hipStream_t);
 
 }  // namespace fmb

@@ -1257,8 +1257,7 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
         if (l < lmin) return true;
         if (!P.dense) {
             tm.begin(ST_M2M, s, ev);
-            hf_m2m<T>(P, l, nrhs, s);
-            tm.end(ST_M2M, s, ev);
+            tm.end(ST_M2M, s, ev, hf_m2m<T>(P, l, nrhs, s));
             return true;
         }
         if (V.ntiles_m2m == 0) return true;
@@ -1285,14 +1284,15 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
             // each target sums its own far-field translations and writes its local expansion; the finest
             // level has a launch of its own while its timer is on
             const bool split = tm.mask >> ST_M2L_FINE & 1u;
-            hf_m2l<T>(P, lmin, split ? L - 1 : L, nrhs, s);
+            nk = hf_m2l<T>(P, lmin, split ? L - 1 : L, nrhs, s);
             if (split) {
                 hipEvent_t ev2 = nullptr;
                 tm.begin(ST_M2L_FINE, s, ev2);
-                hf_m2l<T>(P, L, L, nrhs, s);
-                tm.end(ST_M2L_FINE, s, ev2, 1);
+                const int fine = hf_m2l<T>(P, L, L, nrhs, s);
+                tm.end(ST_M2L_FINE, s, ev2, fine);
+                nk += fine;
             }
-            tm.end(ST_M2L, s, ev, L - lmin + 1);
+            tm.end(ST_M2L, s, ev, nk);
             return true;
         }
         for (int l = lmin; l <= L; ++l) {
@@ -1337,8 +1337,7 @@ bool matvec_step(Plan &P, const cx<T> *a, const cx<T> *b, cx<T> *y, int nrhs, hi
         if (l <= lmin) return true;
         if (!P.dense) {
             tm.begin(ST_L2L, s, ev);
-            hf_l2l<T>(P, l, nrhs, s);
-            tm.end(ST_L2L, s, ev);
+            tm.end(ST_L2L, s, ev, hf_l2l<T>(P, l, nrhs, s));
             return true;
         }
         if (V.ntiles_l2l == 0) return true;

@@ -146,9 +146,10 @@ void build_leaf_nodes(Plan &P, hipStream_t s);
 // rotation / coaxial translations (hf.hip)
 int hf_order(double kabs, double side, double tol);
 void build_hf(Plan &P, hipStream_t s);
-template <typename T> void hf_m2m(Plan &P, int l, int nrhs, hipStream_t s);
-template <typename T> void hf_m2l(Plan &P, int l0, int l1, int nrhs, hipStream_t s);
-template <typename T> void hf_l2l(Plan &P, int l, int nrhs, hipStream_t s);
+// each returns the kernels it launched
+template <typename T> int hf_m2m(Plan &P, int l, int nrhs, hipStream_t s);
+template <typename T> int hf_m2l(Plan &P, int l0, int l1, int nrhs, hipStream_t s);
+template <typename T> int hf_l2l(Plan &P, int l, int nrhs, hipStream_t s);
 void build_corrections(Plan &P, const double *d_pts, const double *d_nrm, const double *d_tri,
                        hipStream_t s);
 void scatter_with_corrections(Plan &P, const void *ys, const void *a, const void *b, void *y, int nrhs,

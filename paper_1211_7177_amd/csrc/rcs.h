@@ -104,7 +104,8 @@ int64_t rcs_csize(const RcsSet &R);
 void rcs_build(RcsSet &R, int64_t npairs, const DevBuf *ofs, const DevBuf *src, const DevBuf &dir, int dir_add,
                const std::vector<int32_t> &cls_of, const std::vector<int32_t> &cdist, hipStream_t s);
 void rcs_split(RcsSet **sets, int nsets, bool f64, int nrhs_max);
+// returns the kernels it launched
 template <typename T>
-void rcs_run(const RcsJob *jobs, int njobs, int nrhs, int nrhs_max, hipStream_t s);
+int rcs_run(const RcsJob *jobs, int njobs, int nrhs, int nrhs_max, hipStream_t s);
 
 }  // namespace fmb

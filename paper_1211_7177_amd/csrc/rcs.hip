@@ -282,7 +282,8 @@ static void launch(double, int P, const RcsArgs &A, unsigned blocks, size_t lds,
 // Consecutive jobs of one order go out as one launch.  A launch holds less than 2^32 threads and sets split over
 // zsplit blocks keep partial sums for part_rhs right-hand sides: wider batches run in slices.
 template <typename T>
-void rcs_run(const RcsJob *jobs, int njobs, int nrhs, int nrhs_max, hipStream_t s) {
+int rcs_run(const RcsJob *jobs, int njobs, int nrhs, int nrhs_max, hipStream_t s) {
+    int nk = 0;
     for (int a = 0; a < njobs;) {
         const RcsSet &F = *jobs[a].set;
         int b = a, slice = nrhs;
@@ -330,6 +331,7 @@ void rcs_run(const RcsJob *jobs, int njobs, int nrhs, int nrhs_max, hipStream_t 
             }
             if (blocks == 0) continue;
             launch(T(0), F.P, A, (unsigned)blocks, lds, s);
+            ++nk;
             SumArgs Z{};
             Z.nrhs = nr;
             Z.nrhs_max = nrhs_max;
@@ -347,12 +349,14 @@ void rcs_run(const RcsJob *jobs, int njobs, int nrhs, int nrhs_max, hipStream_t 
             if (Z.nset) {
                 k_rcs_sum<T><<<(unsigned)((Z.first[Z.nset] + 255) / 256), 256, 0, s>>>(Z);
                 FMB_LAUNCH_CHECK();
+                ++nk;
             }
         }
         a = b;
     }
+    return nk;
 }
-template void rcs_run<float>(const RcsJob *, int, int, int, hipStream_t);
-template void rcs_run<double>(const RcsJob *, int, int, int, hipStream_t);
+template int rcs_run<float>(const RcsJob *, int, int, int, hipStream_t);
+template int rcs_run<double>(const RcsJob *, int, int, int, hipStream_t);
 
 }  // namespace fmb
