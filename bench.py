@@ -542,12 +542,18 @@ def torus_section(args, log):
     p2p_tf = p2p_fl / (p2p_ms / mv32 * 1e-3) / 1e12
     tr_fl = sr_flops(inf) * mv32
     tr_by = sr_bytes(inf, 8) * mv32
+    bf3 = args.translate32 == "bf16x3" and 2 <= args.order32 <= 9
+    if bf3:
+        tr_name, tr_peak = "k_translate_bf3 S|R (role 1; split-BF16 MFMA, FP32 accumulate)", PEAK["bf16_TF"]
+    elif 1 <= args.order32 <= 7:
+        tr_name, tr_peak = "k_translate_os S|R (FP32 MFMA)", PEAK["fp32_TF"]
+    else:
+        tr_name, tr_peak = "k_rcs S|R (rotation / coaxial shift / rotation, FP32 MFMA)", PEAK["fp32_TF"]
+        lv = list(zip(inf["m2l_pairs"], inf["order_level"]))
+        tr_fl = sum(q * hf_translation_flops(p) for q, p in lv) * mv32
+        tr_by = sum(q * 2.0 * 3 * p * p * 8 for q, p in lv) * mv32
     tr_tf = tr_fl / (tr_ms * 1e-3) / 1e12
     tr_gbs = tr_by / (tr_ms * 1e-3) / 1e9
-    if args.translate32 == "bf16x3":
-        tr_name, tr_peak = "k_translate_bf3 S|R (role 1; split-BF16 MFMA, FP32 accumulate)", PEAK["bf16_TF"]
-    else:
-        tr_name, tr_peak = "k_translate_os S|R (FP32 MFMA)", PEAK["fp32_TF"]
     # below the ridge point (peak flops / HBM bandwidth) the translations are bound by memory
     tr_hbm = tr_fl / tr_by < tr_peak * 1e12 / (PEAK["hbm_GBs"] * 1e9)
     stages_rf = {
@@ -564,8 +570,7 @@ def torus_section(args, log):
                       "avg_launch_ms": tr_ms / max(1, tr_launches), "launches": tr_launches,
                       "mfma_view": {"achieved_TFLOPs": tr_tf, "peak_TFLOPs": tr_peak, "frac": tr_tf / tr_peak}},
     }
-    stages_rf["translate"]["traffic"] = measured_traffic("k_translate_bf3 S|R") if args.translate32 == "bf16x3" \
-        else None
+    stages_rf["translate"]["traffic"] = measured_traffic("k_translate_bf3 S|R") if bf3 else None
     stages_rf["p2p"]["traffic"] = measured_traffic("k_p2p32")
     dominant = "p2p" if p2p_ms >= tr_ms else "translate"
     roofline = dict(stages_rf[dominant])
