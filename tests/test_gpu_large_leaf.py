@@ -45,3 +45,22 @@ def test_several_right_hand_sides_at_large_leaf_orders(body, order, depth, waves
     print("large leaf order %d depth %d err %.2e" % (order, depth, err), flush=True)
     assert err <= 4 * 10.0 ** (-order / 2.8) + 1e-12
     P.close()
+
+
+@pytest.mark.parametrize("k,order", [(16.0, 25), (22.0, 32), (23.0, 33), (30.0, 40)])
+def test_single_precision_leaves_many_wavelengths_wide(body, k, order):
+    """Leaves of half the unit sphere's radius at k (excess-bandwidth rule for 1e-4): both columns of a batch keep what
+    the plan was asked for, 1e-4."""
+    from paper_1211_7177_amd import Plan
+    q, a, b, _ = body
+    print("large leaf fp32 k", k, flush=True)
+    P = Plan(q["points"], q["normals"], q["weights"], k, 0, depth=2, precision="fp32", nrhs_max=2, corr="none",
+             point_tri=q["point_tri"], tol=1e-4)
+    assert P.info()["order"] == order
+    y = P.matvec(*(torch.as_tensor(u[:2], device="cuda").to(torch.complex64) for u in (a, b))).cpu().numpy()
+    ref = point_sum_c(q["points"], q["normals"], q["weights"], q["point_tri"], k, a[:2], b[:2])
+    for r in range(2):
+        err = np.linalg.norm(y[r] - ref[r]) / np.linalg.norm(ref[r])
+        print("large leaf fp32 order %d err %.2e" % (order, err), flush=True)
+        assert err <= 1e-4
+    P.close()
