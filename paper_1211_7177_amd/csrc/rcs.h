@@ -65,7 +65,7 @@ constexpr RcsMap rcs_map(int P, int W) {
 struct RcsSet {
     bool on = false;
     int ps = 0, pd = 0, P = 0;    // source and destination orders, the kernel's order
-    int ncls = 0, tg = 1, ngroups = 0, zsplit = 1, part_rhs = 1, nc = 1, waves = 4;
+    int ncls = 0, tg = 1, ngroups = 0, zsplit = 1, nc = 1, waves = 4;
     int64_t nbox = 0;
     DevBuf gcls;                  // i32[ngroups][ncls + 1] bounds of each class's pairs
     DevBuf ent;                   // i32[npairs][2]: source box; destination, reflection, turn, direction (k_rcs_lists)
@@ -73,7 +73,7 @@ struct RcsSet {
     DevBuf ph;                    // e^{i m phi} / sqrt 2 (1 / 2 at m = 0) of each direction, phs entries apart
     int phs = 0;
     DevBuf cdist;                 // i32[ncls] distance of each class (none: one distance)
-    DevBuf part;                  // zsplit > 1: [zsplit][nbox][part_rhs][3][pd^2] partial sums
+    DevBuf part;                  // zsplit > 1: [zsplit][nbox][nrhs_max][3][pd^2] partial sums
     size_t lds = 0;
     size_t bytes() const {
         return gcls.bytes + ent.bytes + W.bytes + C.bytes + ph.bytes + cdist.bytes + part.bytes;

@@ -14,7 +14,7 @@ namespace {
 struct SumArgs {
     int nset, nrhs, nrhs_max;
     int64_t first[RCS_MAXLEV + 1];
-    int zsplit[RCS_MAXLEV], part_rhs[RCS_MAXLEV], blk[RCS_MAXLEV];
+    int zsplit[RCS_MAXLEV], blk[RCS_MAXLEV];
     const void *part[RCS_MAXLEV];
     void *D[RCS_MAXLEV];
 };
@@ -27,8 +27,8 @@ __global__ void k_rcs_sum(SumArgs A) {
     i -= A.first[l];
     const int blk = A.blk[l];
     const int64_t per = (int64_t)A.nrhs * blk, box = i / per, e = i - box * per;
-    const int64_t st = (A.first[l + 1] - A.first[l]) / per * A.part_rhs[l] * blk;
-    const cx<T> *p = (const cx<T> *)A.part[l] + box * A.part_rhs[l] * blk + e;
+    const int64_t st = (A.first[l + 1] - A.first[l]) / per * A.nrhs_max * blk;
+    const cx<T> *p = (const cx<T> *)A.part[l] + box * A.nrhs_max * blk + e;
     cx<T> s = p[0];
     for (int z = 1; z < A.zsplit[l]; ++z) s += p[z * st];
     ((cx<T> *)A.D[l])[box * A.nrhs_max * blk + e] = s;
@@ -237,9 +237,11 @@ void rcs_build(RcsSet &R, int64_t npairs, const DevBuf *ofs, const DevBuf *src, 
 }
 
 // Sets of few blocks split each group's tiles over zsplit of them, so that a launch over all levels holds at least
-// twice what the CUs take at once (by LDS, eight blocks at most); the partial sums stay under 256 MB.  S|R of all
-// levels, unsplit -> split: ring 148k FP64 p = 16 1.82 -> 1.34 ms, 26k ellipsoid FP32 p = 12 1.0 -> 0.48 ms, sphere
-// 3,840 nodes FP64 p = 16 (123 blocks) 0.30 ms at 6 ways, 0.28 at 8 to 16, 0.30 at 25.
+// twice what the CUs take at once (by LDS, eight blocks at most); the partial sums stay under 100 MB a set at every
+// order and batch.  S|R of all levels, unsplit -> split: ring 148k FP64 p = 16 1.82 -> 1.34 ms, 26k ellipsoid FP32
+// p = 12 1.0 -> 0.48 ms, sphere 3,840 nodes FP64 p = 16 (123 blocks) 0.30 ms at 6 ways, 0.28 at 8 to 16, 0.30 at 25.
+// The split follows the plan's largest batch, not the call's, so that a column's sums do not depend on how many there
+// are; one column on a plan for eight takes 424 us where one on a plan for one takes 342 (sphere FP64 p = 16).
 void rcs_split(RcsSet **sets, int nsets, bool f64, int nrhs_max) {
     int64_t blocks = 0;
     size_t lds = 1;
@@ -254,10 +256,8 @@ void rcs_split(RcsSet **sets, int nsets, bool f64, int nrhs_max) {
     if (z <= 1) return;
     for (int i = 0; i < nsets; ++i) {
         RcsSet &R = *sets[i];
-        const size_t per = (size_t)z * R.nbox * 3 * R.pd * R.pd * (f64 ? 16 : 8);
         R.zsplit = z;
-        R.part_rhs = (int)std::max<size_t>(1, std::min<size_t>((size_t)nrhs_max, ((size_t)256 << 20) / per));
-        R.part.alloc(per * R.part_rhs);
+        R.part.alloc((size_t)z * R.nbox * nrhs_max * 3 * R.pd * R.pd * (f64 ? 16 : 8));
     }
 }
 
@@ -279,8 +279,7 @@ static void launch(double, int P, const RcsArgs &A, unsigned blocks, size_t lds,
     throw Status{FMB_EINVAL, "no translation kernel of this order"};
 }
 
-// Consecutive jobs of one order go out as one launch.  A launch holds less than 2^32 threads and sets split over
-// zsplit blocks keep partial sums for part_rhs right-hand sides: wider batches run in slices.
+// Consecutive jobs of one order go out as one launch.  A launch holds less than 2^32 threads: wider batches run in slices.
 template <typename T>
 int rcs_run(const RcsJob *jobs, int njobs, int nrhs, int nrhs_max, hipStream_t s) {
     int nk = 0;
@@ -291,7 +290,6 @@ int rcs_run(const RcsJob *jobs, int njobs, int nrhs, int nrhs_max, hipStream_t s
         for (; b < njobs && b - a < RCS_MAXLEV; ++b) {
             const RcsSet &R = *jobs[b].set;
             if (R.P != F.P) break;
-            if (R.zsplit > 1) slice = std::min(slice, R.part_rhs);
             per += (int64_t)R.ngroups * R.zsplit * (3 / R.nc) * R.waves * 64;
         }
         FMB_REQUIRE(per < (int64_t)1 << 32, "too many translation blocks");
@@ -325,7 +323,6 @@ int rcs_run(const RcsJob *jobs, int njobs, int nrhs, int nrhs_max, hipStream_t s
                 V.S = (const cx<T> *)jobs[i].S + (int64_t)r0 * 3 * R.ps * R.ps;
                 V.D = (cx<T> *)jobs[i].D + (int64_t)r0 * 3 * R.pd * R.pd;
                 V.part = R.part.p;
-                V.part_rhs = R.part_rhs;
                 blocks += (int64_t)R.ngroups * R.zsplit * (3 / R.nc) * nr;
                 lds = std::max(lds, R.lds);
             }
@@ -340,7 +337,6 @@ int rcs_run(const RcsJob *jobs, int njobs, int nrhs, int nrhs_max, hipStream_t s
                 if (R.zsplit == 1) continue;
                 const int l = Z.nset++;
                 Z.zsplit[l] = R.zsplit;
-                Z.part_rhs[l] = R.part_rhs;
                 Z.blk[l] = 3 * R.pd * R.pd;
                 Z.part[l] = R.part.p;
                 Z.D[l] = A.lev[i - a].D;

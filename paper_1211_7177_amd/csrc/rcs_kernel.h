@@ -49,7 +49,7 @@ constexpr int RCS_MAXLEV = 10;
 
 // one set of a launch
 struct RcsLev {
-    int blk0, ngroups, zsplit, tg, ncls, ps, pd, phs, nbox, accumulate, part_rhs;
+    int blk0, ngroups, zsplit, tg, ncls, ps, pd, phs, nbox, accumulate;
     const int32_t *gcls, *cdist;
     const int2 *ent;
     const void *ph, *W, *C, *S;
@@ -391,14 +391,10 @@ __global__ void __launch_bounds__(WAVES * 64, MINW) k_rcs(RcsArgs A) {
     }
     rcs_sync();
     C *out = Dg;
-    int64_t obox = dbox;
-    if (V.zsplit > 1) {
-        out = (C *)V.part + ((((int64_t)z * V.nbox + b0) * V.part_rhs + r) * 3 + ch) * D2;
-        obox = (int64_t)V.part_rhs * 3 * D2;
-    }
+    if (V.zsplit > 1) out = (C *)V.part + ((((int64_t)z * V.nbox + b0) * A.nrhs_max + r) * 3 + ch) * D2;
     for (int t = tid; t < nb * NC * D2; t += TPB) {
         const int b = t / (NC * D2), e = t - b * NC * D2;
-        out[b * obox + e] = acc[t];
+        out[b * dbox + e] = acc[t];
     }
 }
 
