@@ -150,7 +150,7 @@ int fmm_matvec(fmb_plan_t plan, const void *a, const void *b, void *y, int32_t n
  * evaluation.  y, a_bar, b_bar: device [nrhs][n][3] complex of the plan's
  * precision, user node order; none may alias.  Asynchronous on `stream`.
  * The first call allocates a workspace of nrhs_max * n * 12 complex.
- * FMB_EINVAL for FP64 plans of order above 23.
+ * FMB_EINVAL for FP64 plans of order above 23 and FP32 plans of order above 36.
  */
 int fmm_matvec_adjoint(fmb_plan_t plan, const void *y, void *a_bar, void *b_bar, int32_t nrhs,
                        void *stream);

@@ -376,8 +376,9 @@ void finish_t(Plan &P, const void *y, void *abar, void *bbar, int nrhs, hipStrea
 
 void adjoint_prepare(Plan &P) {
     const size_t cs = P.precision == FMB_FP64 ? sizeof(cx<double>) : sizeof(cx<float>);
-    const size_t N1 = P.order + 1;
-    FMB_REQUIRE((4 * (N1 * N1 + 1) + 64 * N1) * cs <= 65536, "the adjoint's far-field evaluation supports orders up to 23 in FP64");
+    // the entry point's limits; k_adj_l2p's instances and LDS would hold 39
+    FMB_REQUIRE(P.order <= (P.precision == FMB_FP64 ? 23 : 36),
+                "the adjoint's far-field evaluation supports orders up to 23 in FP64 and 36 in FP32");
     const size_t need = (size_t)P.nrhs_max * P.n * 12 * cs;
     if (P.aws.bytes < need) P.aws.alloc(need);
 }

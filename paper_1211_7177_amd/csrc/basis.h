@@ -15,7 +15,7 @@ namespace fmb {
 //   Q_n^m = la[n][m] (x Q_{n-1}^m - lb[n][m] Q_{n-2}^m)            (n > m, Q_{m-1}^m = 0)
 template <typename T>
 struct BasisTab {
-    const T *la, *lb, *qmm, *q1;     // [(N+1)^2] (row n, column m), [(N+1)^2], [N+1], [N+1]
+    const T *la, *lb, *qmm;          // [(N+1)^2] (row n, column m), [(N+1)^2], [N+1]
     const T *gco;                    // [P2][6] gradient coefficients of coefficient idx (mu = -m)
     int N;
 };
@@ -27,8 +27,7 @@ __device__ inline BasisTab<T> basis_tab(const T *tab, int N) {
     b.la = tab;
     b.lb = tab + NN;
     b.qmm = tab + 2 * NN;
-    b.q1 = tab + 2 * NN + (N + 1);
-    b.gco = tab + 2 * NN + 2 * (N + 1);
+    b.gco = tab + 2 * NN + (N + 1);
     b.N = N;
     return b;
 }

@@ -192,44 +192,32 @@ __device__ inline double fast_rsqrt(double x) {
 __device__ inline float fast_rsqrt(float x) { return rsqrtf(x); }
 
 // ---------------------------------------------------------------------------
-// spherical Bessel functions of complex argument (FP64 or FP32)
+// spherical Bessel functions of complex argument
 // ---------------------------------------------------------------------------
 //
 // j_n(z), n = 0..N: Miller's method in ratio form.  r_n = j_n / j_{n-1}
 // satisfies r_n = z / (2n + 1 - z r_{n+1}); started far above N with r = 0 it
 // is stable for every z, including z -> 0 where r_n -> z/(2n+1).  Then
 // j_0 = sin z / z (series for small |z|) and j_n = j_{n-1} r_n.
-// z / den for the ratio recurrence (|den| >= 1 there, no scaling needed):
-// FP32 uses the hardware reciprocal.
-__device__ inline cx<double> cdiv_ratio(cx<double> a, cx<double> b) { return cdiv(a, b); }
-__device__ inline cx<float> cdiv_ratio(cx<float> a, cx<float> b) {
-    const float inv = __builtin_amdgcn_rcpf(b.re * b.re + b.im * b.im);
-    return mk((a.re * b.re + a.im * b.im) * inv, (a.im * b.re - a.re * b.im) * inv);
-}
-
-template <typename T>
-__device__ inline void sph_bessel_j(cx<T> z, int N, cx<T> *out) {
-    const T az = (T)sqrt(abs2(z));
-    if (az < T(1e-30)) {
-        out[0] = mk(T(1), T(0));
-        for (int n = 1; n <= N; ++n) out[n] = mk(T(0), T(0));
+__device__ inline void sph_bessel_j(cx<double> z, int N, cx<double> *out) {
+    const double az = sqrt(abs2(z));
+    if (az < 1e-30) {
+        out[0] = mk(1.0, 0.0);
+        for (int n = 1; n <= N; ++n) out[n] = mk(0.0, 0.0);
         return;
     }
-    // FP32 needs fewer extra terms: the neglected tail scales like the product
-    // of |z / (2n + 1)|^2 over the skipped degrees
-    const int extra = sizeof(T) == sizeof(float) ? 8 + (int)(T(1.2) * az) : 16 + (int)az;
-    const int start = N + extra;
-    cx<T> r = mk(T(0), T(0));
+    const int start = N + 16 + (int)az;
+    cx<double> r = mk(0.0, 0.0);
     // walk down from `start`, store ratios for n <= N in out[] temporarily
     for (int n = start; n >= 1; --n) {
-        cx<T> den = mk(T(2 * n + 1), T(0)) - z * r;
-        r = cdiv_ratio(z, den);
+        cx<double> den = mk(2.0 * n + 1.0, 0.0) - z * r;
+        r = cdiv(z, den);
         if (n <= N) out[n] = r;
     }
-    cx<T> j0;
-    if (az < T(1e-3)) {
-        cx<T> z2 = z * z;
-        j0 = mk(T(1), T(0)) - z2 * (T(1) / T(6)) + (z2 * z2) * (T(1) / T(120));
+    cx<double> j0;
+    if (az < 1e-3) {
+        cx<double> z2 = z * z;
+        j0 = mk(1.0, 0.0) - z2 * (1.0 / 6.0) + (z2 * z2) * (1.0 / 120.0);
     } else {
         j0 = cdiv(csin_(z), z);
     }

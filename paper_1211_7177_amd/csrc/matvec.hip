@@ -27,9 +27,6 @@ namespace {
 
 constexpr int TPB = 256;
 
-template <typename T>
-__device__ inline cx<T> tc(cx<double> z) { return mk((T)z.re, (T)z.im); }
-
 // ---------------------------------------------------------------- gather
 template <typename T>
 __global__ void k_gather_src(const cx<T> *__restrict__ a, const cx<T> *__restrict__ b, const int32_t *__restrict__ perm,

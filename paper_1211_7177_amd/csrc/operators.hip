@@ -274,19 +274,18 @@ __global__ void k_leaf_nodes(const int32_t *__restrict__ start, const double *__
 }  // namespace
 
 // Recurrence constants for the basis kernels (P2M, L2P), N = order:
-//   la[n][m] = sqrt((4n^2 - 1) / (n^2 - m^2)), lb[n][m] = sqrt(((n-1)^2 - m^2) / (4(n-1)^2 - 1))  (n >= m + 2),
-//   qmm[m] = Q_m^m / (sin th)^m = (4 pi)^{-1/2} prod_{i <= m} sqrt((2i + 1) / 2i),  q1[m] = sqrt(2m + 3),
+//   la[n][m] = sqrt((4n^2 - 1) / (n^2 - m^2)), lb[n][m] = sqrt(((n-1)^2 - m^2) / (4(n-1)^2 - 1))  (n > m),
+//   qmm[m] = Q_m^m / (sin th)^m = (4 pi)^{-1/2} prod_{i <= m} sqrt((2i + 1) / 2i),
 // then, per coefficient idx = n^2 + n + m (n < order) with mu = -m, the six
-// coefficients and R-table indices of the gradient recurrences
+// coefficients of the gradient recurrences
 //   d_z R_n^mu = k (-A R_{n+1}^mu + B R_{n-1}^mu)
 //   d_+ R_n^mu = k s_u (-c R_{n+1}^{mu+1} + d R_{n-1}^{mu+1})    (s_u = sign of mu, +1 at 0)
-//   d_- R_n^mu = k s_d (-e R_{n+1}^{mu-1} + f R_{n-1}^{mu-1})    (s_d = +1 for mu > 0, else -1)
-// and the index of R_n^mu itself; terms outside 0 <= n <= N, |mu| <= n point
-// at the zero entry (N+1)^2.
+//   d_- R_n^mu = k s_d (-e R_{n+1}^{mu-1} + f R_{n-1}^{mu-1})    (s_d = +1 for mu > 0, else -1);
+// those of functions that do not exist (|mu +- 1| > n - 1) are zero.
 void build_basis_tables(Plan &P, hipStream_t s) {
     const int N = P.order, NN = (N + 1) * (N + 1), P2 = P.order * P.order;
-    std::vector<double> t((size_t)2 * NN + 2 * (N + 1) + (size_t)6 * P2, 0.0);
-    double *la = t.data(), *lb = la + NN, *qmm = lb + NN, *q1 = qmm + (N + 1), *gco = q1 + (N + 1);
+    std::vector<double> t((size_t)2 * NN + (N + 1) + (size_t)6 * P2, 0.0);
+    double *la = t.data(), *lb = la + NN, *qmm = lb + NN, *gco = qmm + (N + 1);
     for (int m = 0; m <= N; ++m)
         for (int n = m + 1; n <= N; ++n) {
             la[n * (N + 1) + m] = std::sqrt((4.0 * n * n - 1.0) / ((double)n * n - (double)m * m));
@@ -294,7 +293,6 @@ void build_basis_tables(Plan &P, hipStream_t s) {
         }
     qmm[0] = 0.28209479177387814347;
     for (int m = 1; m <= N; ++m) qmm[m] = qmm[m - 1] * std::sqrt((2.0 * m + 1.0) / (2.0 * m));
-    for (int m = 0; m <= N; ++m) q1[m] = std::sqrt(2.0 * m + 3.0);
     for (int idx = 0; idx < P2; ++idx) {
         int n = 0;
         while ((n + 1) * (n + 1) <= idx) ++n;

@@ -64,3 +64,27 @@ def test_single_precision_leaves_many_wavelengths_wide(body, k, order):
         print("large leaf fp32 order %d err %.2e" % (order, err), flush=True)
         assert err <= 1e-4
     P.close()
+
+
+@pytest.mark.parametrize("precision,order,k,refused", [("fp64", 23, 0.5, False), ("fp64", 24, 0.5, True),
+                                                       ("fp32", 36, 26.0, False), ("fp32", 37, 27.0, True)])
+def test_adjoint_orders(body, precision, order, k, refused):
+    """The adjoint takes leaf orders up to 23 in double and 36 in single precision: there <A(a, b), y> =
+    <(a, b), A^H y> holds to rounding (1e-12 and 1e-4 of the norms)."""
+    from paper_1211_7177_amd import Plan
+    from paper_1211_7177_amd._abi import FmbError
+    q, a, b, _ = body
+    tol = 10.0 ** (-(order - 0.5) / 2.8) if precision == "fp64" else 1e-4
+    P = Plan(q["points"], q["normals"], q["weights"], k, 0, depth=2, precision=precision, corr="none",
+             point_tri=q["point_tri"], tol=tol)
+    assert P.info()["order"] == order
+    y = torch.as_tensor(a[2], device="cuda").to(P.cdtype)
+    if refused:
+        with pytest.raises(FmbError, match="orders up to 23 in FP64"):
+            P.matvec_adjoint(y)
+    else:
+        out = P.matvec(*(torch.as_tensor(u[0], device="cuda").to(P.cdtype) for u in (a, b))).cpu().numpy().astype(complex)
+        va, vb = (u.cpu().numpy().astype(complex) for u in P.matvec_adjoint(y))
+        gap = abs(np.vdot(a[2], out) - np.vdot(va, a[0]) - np.vdot(vb, b[0]))
+        assert gap <= (1e-12 if precision == "fp64" else 1e-4) * np.linalg.norm(a[2]) * np.linalg.norm(out)
+    P.close()
