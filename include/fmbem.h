@@ -75,7 +75,8 @@ typedef struct {
  * Translation arithmetic of FP32 plans.  FMB_TRANSLATE_BF16X3 splits operator
  * and coefficients into BF16 high and low parts and forms hi*hi + hi*lo +
  * lo*hi on the BF16 matrix cores with FP32 accumulation (about 1e-5 relative
- * per product); it applies to orders p <= 9 and falls back to FP32 otherwise.
+ * per product); it applies to plans of one order 2 <= p <= 9 and falls back to
+ * FP32 otherwise.
  */
 enum { FMB_TRANSLATE_DEFAULT = 0, FMB_TRANSLATE_FP32 = 1, FMB_TRANSLATE_BF16X3 = 2 };
 
@@ -105,8 +106,10 @@ int fmb_plan_opts_default(fmb_plan_opts *opts);
  *   points   host f64[n][3]   node positions s_beta
  *   normals  host f64[n][3]   unit normals (|n| within 1e-6 of 1), outward
  *   weights  host f64[n]      Nystrom weights w_beta > 0 (eq. 2.8)
- *   order    p >= 1: degrees 0..p-1 kept at every level (eq. 2.17 cut), translations
- *            as dense per-offset operators (p <= 24);
+ *   order    p >= 1: degrees 0..p-1 kept at every level (eq. 2.17 cut), p <= 24;
+ *            translations as dense per-offset operators for small p (FP64 p <= 4,
+ *            FP32 p <= 7, split-BF16 p <= 9), by rotation, coaxial shift and rotation
+ *            back above;
  *            p <= 0: an order per level chosen for opts->tol (default 1e-6 FP64,
  *            1e-4 FP32): p_l = max(2.8 d0, k d + 1.8 d0^(2/3) (k d)^(1/3)) with
  *            d0 = -log10 tol and d the level's box diameter, so that boxes many

@@ -101,7 +101,7 @@ struct Plan {
     bool far_on() const { return far_lmin <= depth; }
     // order <= 0 at fmm_plan: an order per level for the tolerance `tol` (order = the leaf level's order)
     bool hf = false;
-    // FP32 plans of one small order translate by dense operators, one GEMM per offset (matvec.hip); all others by
+    // plans of one small order translate by dense operators, one GEMM per offset (matvec.hip); all others by
     // rotation and coaxial shift (hf.hip)
     bool dense = false;
     double tol = 0.0;

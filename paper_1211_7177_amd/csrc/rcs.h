@@ -13,7 +13,10 @@ constexpr int RCS_PMAX32 = 32, RCS_PMAX64 = 24;     // largest order of a set (s
 constexpr int RCS_TILE = 8;                         // pairs of one class that run through the matrix cores together
 constexpr size_t RCS_LDS_MAX = 160 * 1024 - 1024;   // beside the kernel's own arrays
 
-// the order whose kernel serves order p: all to 12, then those that per-level plans meet most and every second
+// The order whose kernel serves order p: all to 12, then every second, and 17, 21 and 23.  17 and 23 are the order rule's
+// for 1e-6 and 1e-8, 21 is next above the leaves of bodies many wavelengths across.  A product on a kernel of their own
+// against the next larger (torus 60,000 nodes, ms): FP64 17 2.55 / 3.19, 21 3.99 / 4.22, 23 4.96 / 5.18; FP32 1.28 / 1.36,
+// 1.91 / 2.04, 2.99 / 3.13.  13, 15, 19 and the odd ones above 24 have not been measured.
 constexpr int rcs_order(int p) {
     return p <= 12 || p == 17 || p == 21 || p == 23 ? (p < 2 ? 2 : p) : (p + 1) / 2 * 2;
 }
