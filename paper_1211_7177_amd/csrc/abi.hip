@@ -183,6 +183,15 @@ int fmm_plan(const double *points, const double *normals, const double *weights,
         } else {
             for (int l = 0; l <= P.depth; ++l) P.lv[l].p = order;
             P.dense = dense_order(P.precision, P.translate_mode, order);
+            // FP64 plans and those of order 1 rotate where a slot for every pair and column would take more than 16 GB
+            // (60,000-node torus at FP64 order 4: from 163 columns; 1,024 would take 108 GB).  The rotations need none and
+            // are 1.2 to 1.4 times slower there, so batches that fill the memory with vectors keep it.
+            if (P.precision == FMB_FP64 || order == 1) {
+                double slots = 0.0;
+                for (int l = std::max(2, P.far_lmin); l <= P.depth; ++l) slots += (double)P.lv[l].nff;
+                const double bytes = slots * P.nrhs_max * 3.0 * order * order * (P.precision == FMB_FP64 ? 16 : 8);
+                P.dense = P.dense && bytes <= 16.0 * (1 << 30);
+            }
         }
         build_basis_tables(P, s);
         if (P.far_on()) build_leaf_nodes(P, s);

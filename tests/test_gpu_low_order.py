@@ -63,3 +63,20 @@ def test_dense_and_rotated_translations_agree(body, order):
     assert torch.linalg.norm(d - r) <= 1e-13 * torch.linalg.norm(d)
     D.close()
     R.close()
+
+
+def test_wide_plans_rotate():
+    """A slot for every pair and column would take more than 16 GB in a plan for 1,024: it rotates (no sums over slots
+    are timed) and agrees with the dense plan for one to rounding (1e-13)."""
+    q = nystrom3(meshes.icosphere(8))
+    n = q["points"].shape[0]
+    a, b = (torch.as_tensor(complex_normal((n, 3), s), device="cuda") for s in (64, 65))
+    y = []
+    for wide in (1, 1024):
+        P = _plan(q, 4, "fp64", nrhs_max=wide)
+        assert (sum(P.info()["m2l_pairs"]) * wide * 3 * 16 * 16 > 16 << 30) == (wide > 1)
+        P.profile(True)
+        y.append(P.matvec(a, b))
+        assert (P.profile_read()["sums"][1] > 0) == (wide == 1)
+        P.close()
+    assert torch.linalg.norm(y[0] - y[1]) <= 1e-13 * torch.linalg.norm(y[0])
